@@ -81,6 +81,32 @@ def test_quantize_rows_bit_exact(level, cols):
     assert not len(bad), (bad[:5], codes[tuple(bad[0])], want[tuple(bad[0])])
 
 
+@pytest.mark.parametrize("level", LEVELS)
+@pytest.mark.parametrize("rows,cols", [(1, 32), (300, 8), (5, 4096), (3, 4128), (3, 8192), (3, 8193), (2, 16390)])
+def test_quantize_rows_work_split(level, rows, cols):
+    """Several rows to a workgroup, one, and several workgroups to a row
+    (1024 chunks of 8 columns each); infinities and NaN by the documented
+    formula evaluated element by element."""
+    lv = LEVELS[level]
+    Q = np.float32(W.QMAX[lv])
+    rng = np.random.default_rng(90 + cols)
+    w = (rng.standard_normal((rows, cols)) * 0.02).astype(np.float16)
+    w[0, -1] = np.inf
+    w[-1, cols // 2] = np.nan
+    w[-1, 0] = np.float16(2.0 ** -15)
+    codes, scales = gpu_quantize(w, lv)
+    nb = W.n_blocks(cols)
+    v = np.zeros((rows, nb * 32), np.float32)
+    v[:, :cols] = w
+    v = v.reshape(rows, nb, 32)
+    with np.errstate(all="ignore"):
+        s = (np.nanmax(np.abs(v), axis=2) / Q).astype(np.float16)
+        r = np.rint(v / s.astype(np.float32)[:, :, None])
+        c = np.where(s[:, :, None] > 0, np.fmin(np.fmax(r, -Q), Q), 0)  # fmax(NaN, -Q) is -Q
+    assert np.array_equal(scales.view(np.int16), s.view(np.int16))
+    assert np.array_equal(codes, W.pack_codes(c.astype(np.int64).reshape(rows, -1), lv))
+
+
 _cache = {}
 
 
