@@ -24,6 +24,7 @@
 #include <algorithm>
 #include <cmath>
 #include <mutex>
+#include <type_traits>
 #include <vector>
 
 #include "device.hpp"
@@ -37,6 +38,10 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 __device__ __forceinline__ f32x16 mfma32(const u32x4 a, const u32x4 b, f32x16 c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, a),
                                                 __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
+}
+
+__device__ __forceinline__ f32x4 mfma16(const u32x4 a, const u32x4 b, f32x4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
 }
 
 // The GEMMs' activation operands (A) are stored k-step-major: the 16 k
@@ -151,8 +156,8 @@ struct GemmArgs {
   uint16_t* out;         // O: h; DOWN: y (nullable)
   const uint16_t* gain;  // O: g_ffn when the FFN follows (else NULL)
   uint16_t* U;           // O: FFN input fp16(h * g_ffn), k-step-major
-  float* rowsq;          // O: [M][n_tiles] sums of h^2 over each tile's columns; GU: read (NULL: 1 / rms = 1)
-  int rowsq_tiles;       // GU: column tiles of the O GEMM
+  float* rowsq;          // O: [M][rowsq_tiles] sums of h^2 over each 128 columns; GU: read (NULL: 1 / rms = 1)
+  int rowsq_tiles;       // 128-column tiles of H
   uint16_t *Q, *kc, *vc; // QKV outputs: Q [M][nq][d], the KV cache [n_kv][cap][d]
   const float* rope;     // [M][d / 2][2] cos, sin of each rotary angle
   int nq, nkv, d, cap, pos0;
@@ -603,6 +608,530 @@ __global__ void __launch_bounds__(GT, 2) gemm_kernel(GemmArgs g) {
 }
 
 // ---------------------------------------------------------------------------
+// The same GEMM on tiles of 256 tokens x 256 features for longer chunks.
+//
+// The 128 x 128 tile moves 32 KiB of operands per k-tile of 512 matrix cycles
+// through its compute unit's L1 (64 B per cycle: all of it) and 80 KiB through
+// LDS (640 of the 512 cycles at 128 B), so it stops at 30-45% of the matrix
+// rate whatever its schedule. 256 x 256 needs half the L1 traffic per flop, and
+// with 128 x 128 per wave (four waves, one per SIMD, accumulators in all 256
+// AGPRs) 64 KiB of LDS reads per 1024 matrix cycles; eight waves of 128 x 64
+// read 96 KiB there and stayed LDS-bound (1530 cycles per 32 k). 16 x 16 x 32
+// MFMAs, two register sets of fragments: one k-tile multiplies while the next
+// one's fragments are read, 1120 of 1024 cycles per 32 k.
+//
+// Both operands go from memory straight into LDS (16-byte buffer loads with the
+// lds bit, 1 KiB per instruction) through a ring of XNST stages of 32 k, three
+// or four k-tiles ahead: a ring of two 64-k stages waited for memory
+// (1.8 us per 64 k against 1.2 us with the loads left out). The loads are
+// issued in inline asm and waited for by count, since with the compiler's
+// builtin every LDS read waits for all of them; they have no register output.
+// What bounds the kernel now is the card's power: with random operands the
+// clock falls to about 1.3-1.6 GHz under it, and 64 k of a full chip take 1.4 us
+// (1.5 PFLOP/s; a large plain product reaches 1.4-1.5 on this card).
+//
+// LDS layout of a stage: A in blocks of 32 tokens x 16 k (1 KiB: the two halves
+// of the 32 bytes apart, so that 16 tokens' chunks are contiguous). B in blocks
+// of 16 rows x 32 k with the 16-byte chunk c of row r at unit
+// 4 r + (c ^ (r / 2 % 4) ^ (r / 8)): the rows one fragment read takes together lie
+// in different bank groups.
+//
+// Rows past M or N read a valid row instead (their sums are never stored).
+// A k-tile that reaches past K (at most one, the slice's first in the order
+// of work) is loaded through registers and masked.
+// ---------------------------------------------------------------------------
+constexpr int XBM = 256, XBN = 256, XT = 256;
+constexpr int XBK = 32, XNST = 5;
+constexpr int XA = XBM * XBK * 2, XSTAGE = XA + XBN * XBK * 2;  // bytes
+constexpr int XGEMM_LDS_BYTES = XNST * XSTAGE;
+static_assert(XGEMM_LDS_BYTES <= 160 * 1024, "one workgroup per compute unit");
+
+// 16 bytes per lane from r[voff + soff] to LDS byte m0 + 16 * lane. m0 is set
+// by dma_to(), with at least one instruction in between.
+template <int OFF>
+__device__ __forceinline__ void dma_to(uint32_t base) {
+  asm volatile("s_add_u32 m0, %0, %1" : : "s"(__builtin_amdgcn_readfirstlane(base)), "n"(OFF) : "scc", "memory");
+}
+__device__ __forceinline__ void dma16(u32x4 r, uint32_t voff, uint32_t soff) {
+  asm volatile("buffer_load_dwordx4 %0, %1, %2 offen lds"
+               :
+               : "v"(voff), "s"(r), "s"(__builtin_amdgcn_readfirstlane(soff))
+               : "memory");
+}
+
+// The same descriptor as make_rsrc, as four scalar words.
+__device__ __forceinline__ u32x4 rsrc_words(const void* base, uint32_t bytes) {
+  const uint64_t p = reinterpret_cast<uint64_t>(base);
+  return u32x4{static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(p))),
+               static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(p >> 32))) & 0xFFFFu, bytes,
+               0x00020000u};
+}
+
+// f(integral_constant 0), .., f(integral_constant N - 1)
+template <int N, int I = 0, class F>
+__device__ __forceinline__ void each(F&& f) {
+  if constexpr (I < N) {
+    f(std::integral_constant<int, I>{});
+    each<N, I + 1>(f);
+  }
+}
+
+// The epilogue of one wave's 128 tokens x 128 features (from m0, n0), by that
+// wave alone: 64 tokens at a time through its own piece of LDS (fp32 rows of
+// TLD floats), so that 16 lanes cover one token's 128 features with 16-byte
+// accesses; lane l takes features 8 (l % 16).. of tokens l / 16 + 4 j. The
+// global inputs are loaded 16 tokens ahead. k-step-major outputs are staged as
+// fp16 in the front of each token's row, after that row has been read (the
+// lanes of a row read and write it in the same instructions, and a wave's LDS
+// accesses complete in order), and leave as 1 KiB per k-step and 32 tokens. The
+// loops stay rolled: every instruction of an unrolled epilogue is run once per
+// workgroup and comes from memory first (30 us instead of 12 us).
+constexpr int ET = 64;
+constexpr int EPI_RINV = ET * TLD * 4, EPI_WAVE_BYTES = EPI_RINV + 128 * 4;
+
+template <int EPI>
+__device__ __forceinline__ void wave_epilogue(const GemmArgs& g, const f32x4 (&acc)[8][8], char* L, int lane, int m0,
+                                              int n0) {
+  constexpr int PB = 4;  // rows per lane in a batch: 16 tokens
+  float* tl = reinterpret_cast<float*>(L);
+  float* rinv = reinterpret_cast<float*>(L + EPI_RINV);
+  auto lds_sync = [&]() {  // keeps the compiler to the order of a wave's LDS accesses
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  };
+  const int f = 8 * (lane % 16), n = n0 + f;
+  const int qd = g.nq * g.d, kd = g.nkv * g.d;
+  const bool in = n < g.N;
+  const bool norm = EPI == EPI_O && g.gain;
+  // QKV: this lane's head and its first dimension there
+  const bool isq = n < qd, rot = n < qd + kd;
+  const int hn = isq ? n : (rot ? n - qd : n - qd - kd), head = EPI == EPI_QKV ? hn / g.d : 0;
+  const int c = hn - head * g.d;
+  const float sc = EPI == EPI_QKV && isq ? 1.0f / sqrtf(static_cast<float>(g.d)) : 1.f;
+  float gg[8] = {};
+  if (norm && in) unpack8(load16(g.gain + n), gg);
+  auto prefetch = [&](int mb, u32x4 (&p)[2 * PB]) {  // tokens mb + l / 16 + 4 j
+    if (EPI == EPI_GU || !in || (EPI == EPI_QKV && !rot)) return;
+#pragma unroll
+    for (int j = 0; j < PB; ++j) {
+      const int m = min(mb + lane / 16 + 4 * j, g.M - 1);
+      if (EPI == EPI_QKV) {
+        const float* cs = g.rope + (static_cast<int64_t>(m) * (g.d / 2) + c / 2) * 2;
+        p[2 * j] = *reinterpret_cast<const u32x4*>(cs);
+        p[2 * j + 1] = *reinterpret_cast<const u32x4*>(cs + 4);
+      } else {
+        const int64_t e = static_cast<int64_t>(m) * g.H + n;
+        p[2 * j] = load16(g.base + e);
+        if (g.peer) p[2 * j + 1] = load16(g.peer + e);
+      }
+    }
+  };
+  u32x4 cur[2 * PB], nxt[2 * PB];
+  prefetch(m0, cur);
+  if (EPI == EPI_GU) {
+    // 1 / rms of tokens lane and lane + 64 from the sums over 128 columns each
+    float ss[2] = {0.f, 0.f}, odd[2] = {0.f, 0.f};
+    const int nt = g.rowsq ? g.rowsq_tiles : 0;
+    const float* rq0 = g.rowsq + static_cast<int64_t>(min(m0 + lane, g.M - 1)) * nt;
+    const float* rq1 = g.rowsq + static_cast<int64_t>(min(m0 + lane + 64, g.M - 1)) * nt;
+    int k = 0;
+#pragma unroll 4
+    for (; k + 1 < nt; k += 2) {
+      ss[0] += rq0[k];
+      ss[1] += rq1[k];
+      odd[0] += rq0[k + 1];
+      odd[1] += rq1[k + 1];
+    }
+    if (k < nt) {
+      ss[0] += rq0[k];
+      ss[1] += rq1[k];
+    }
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+      rinv[lane + 64 * h] =
+          g.rowsq ? 1.0f / sqrtf((ss[h] + odd[h]) / static_cast<float>(g.H) + g.eps) : 1.f;
+  }
+  auto row8 = [&](int mm, int ff, float (&v)[8]) {
+    const f32x4 lo = *reinterpret_cast<const f32x4*>(tl + mm * TLD + ff);
+    const f32x4 hi = *reinterpret_cast<const f32x4*>(tl + mm * TLD + ff + 4);
+    v[0] = lo.x; v[1] = lo.y; v[2] = lo.z; v[3] = lo.w;
+    v[4] = hi.x; v[5] = hi.y; v[6] = hi.z; v[7] = hi.w;
+  };
+  auto staged = [&](int mm, int ff) { return reinterpret_cast<u32x4*>(reinterpret_cast<uint16_t*>(tl + mm * TLD) + ff); };
+  // ``steps`` k-steps of 16 staged columns to dst's columns col0.. below
+  // limit; columns from valid on (a multiple of 8) are zero
+  auto copy_kmajor = [&](uint16_t* dst, int steps, int col0, int limit, int valid, int ms) {
+    lds_sync();
+    const int h8 = 8 * (lane % 2);
+#pragma unroll 4
+    for (int q = 0; q < 2 * steps; ++q) {
+      const int mm = lane / 2 + 32 * (q & 1), k16 = 16 * (q >> 1), col = col0 + k16;
+      if (ms + mm < g.M && col < limit)
+        *reinterpret_cast<u32x4*>(dst + kmajor(col, ms + mm, g.M) + h8) =
+            col + h8 < valid ? *staged(mm, k16 + h8) : u32x4{0u, 0u, 0u, 0u};
+    }
+  };
+  auto half = [&](auto HALF) {
+    constexpr int hf = decltype(HALF)::value;
+    const int ms = m0 + hf * ET;
+    if (ms >= g.M) return;
+    lds_sync();
+    // accumulator i of tile (a, b): token 16 a + 4 (l / 16) + i, feature 16 b + l % 16
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
+#pragma unroll
+      for (int b = 0; b < 8; ++b)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          tl[(16 * a + 4 * (lane / 16) + i) * TLD + b * 16 + lane % 16] = acc[4 * hf + a][b][i];
+    lds_sync();
+    if (EPI == EPI_GU) {
+      const int fc = 8 * (lane % 8), col0 = (n0 / 128) * 64, col = col0 + fc;
+#pragma unroll 2
+      for (int j = 0; j < ET / 8; ++j) {
+        const int mm = lane / 8 + 8 * j;
+        float gt[8], up[8];
+        row8(mm, fc, gt);
+        row8(mm, 64 + fc, up);
+        const float r = rinv[hf * ET + mm];
+        uint16_t h[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+          const float a = gt[k] * r;
+          h[k] = col + k < g.F ? f2h(a / (1.0f + __expf(-a)) * (up[k] * r)) : static_cast<uint16_t>(0);
+        }
+        *staged(mm, fc) = pack8(h);
+      }
+      copy_kmajor(g.Mo, 4, col0, g.kpad, g.kpad, ms);
+      return;
+    }
+#pragma unroll 1
+    for (int jb = 0; jb < ET / (4 * PB); ++jb) {
+      const int mb = ms + jb * 4 * PB;
+      prefetch(mb + 4 * PB, nxt);
+#pragma unroll
+      for (int j = 0; j < PB; ++j) {
+        const int mm = jb * 4 * PB + lane / 16 + 4 * j, m = ms + mm;
+        float sq = 0.f;
+        if (in && m < g.M) {
+          float v[8];
+          row8(mm, f, v);
+          uint16_t h[8];
+          if (EPI == EPI_QKV) {
+            if (rot) {
+              // rotary pairs (2c, 2c + 1) are adjacent
+              const f32x4 r0 = __builtin_bit_cast(f32x4, cur[2 * j]), r1 = __builtin_bit_cast(f32x4, cur[2 * j + 1]);
+              const float co[4] = {r0.x, r0.z, r1.x, r1.z}, si[4] = {r0.y, r0.w, r1.y, r1.w};
+#pragma unroll
+              for (int k = 0; k < 4; ++k) {
+                h[2 * k] = f2h((v[2 * k] * co[k] - v[2 * k + 1] * si[k]) * sc);
+                h[2 * k + 1] = f2h((v[2 * k] * si[k] + v[2 * k + 1] * co[k]) * sc);
+              }
+            } else {
+#pragma unroll
+              for (int k = 0; k < 8; ++k) h[k] = f2h(v[k]);
+            }
+            uint16_t* dst = isq ? g.Q + (static_cast<int64_t>(m) * g.nq + head) * g.d
+                                : (rot ? g.kc : g.vc) + (static_cast<int64_t>(head) * g.cap + g.pos0 + m) * g.d;
+            *reinterpret_cast<u32x4*>(dst + c) = pack8(h);
+          } else {
+            // partial = fp16(p); out = fp16(base + p + peer); for O with the
+            // FFN to follow also the FFN input and the sums of out^2
+            float b[8], pe[8];
+            unpack8(cur[2 * j], b);
+            if (g.peer) unpack8(cur[2 * j + 1], pe);
+            const int64_t e = static_cast<int64_t>(m) * g.H + n;
+            uint16_t oh[8], uh[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+              h[k] = f2h(v[k]);
+              oh[k] = f2h(b[k] + v[k] + (g.peer ? pe[k] : 0.f));
+              if (norm) {
+                const float o = h2f(oh[k]);
+                sq = fmaf(o, o, sq);
+                uh[k] = f2h(o * gg[k]);
+              }
+            }
+            *reinterpret_cast<u32x4*>(g.partial + e) = pack8(h);
+            if (g.out) *reinterpret_cast<u32x4*>(g.out + e) = pack8(oh);
+            if (norm) *staged(mm, f) = pack8(uh);
+          }
+        }
+        if (norm) {
+          sq = sum16(sq);
+          if (lane % 16 == 0 && m < g.M && n0 < g.N) g.rowsq[static_cast<int64_t>(m) * g.rowsq_tiles + n0 / GBN] = sq;
+        }
+      }
+#pragma unroll
+      for (int j = 0; j < 2 * PB; ++j) cur[j] = nxt[j];
+    }
+    if (norm) copy_kmajor(g.U, GBN / 16, n0, (g.H + 15) / 16 * 16, g.H, ms);
+  };
+  half(std::integral_constant<int, 0>{});
+  half(std::integral_constant<int, 1>{});
+}
+
+template <int EPI, bool SPLIT>
+__global__ void __launch_bounds__(XT, 1) gemm256_kernel(GemmArgs g) {
+  extern __shared__ __attribute__((aligned(16))) uint16_t lds[];
+  // the same XCD-aware walk as gemm_kernel's
+  const int id = blockIdx.x;
+  const int groups = (g.n_tiles * g.splits + 7) / 8;
+  const int j = id / 8;
+  const int bm = min(g.m_tiles, RASTER_M);
+  const int blk = j / (bm * groups);
+  const int rows = min(bm, g.m_tiles - blk * bm);
+  const int rr = j - blk * bm * groups;
+  const int unit = (rr / rows) * 8 + id % 8;
+  const int m_tile = blk * bm + rr % rows;
+  static_assert(4 * EPI_WAVE_BYTES <= XGEMM_LDS_BYTES, "the epilogue's LDS");
+  if (unit >= g.n_tiles * g.splits) return;
+  const int n_tile = unit % g.n_tiles, split = unit / g.n_tiles;
+  const int m0 = m_tile * XBM, n0 = n_tile * XBN;
+  const int t = threadIdx.x, lane = t % kWave;
+  const int wave = __builtin_amdgcn_readfirstlane(t / kWave);
+  const int KT = (g.K + XBK - 1) / XBK;
+  const int kt0 = split * g.kps * (GBK / XBK);
+  const int kt_end = min(kt0 + g.kps * (GBK / XBK), KT);
+  const int nkt = kt_end - kt0;
+  const bool tail = kt_end == KT && g.K % XBK != 0;  // the slice holds the partial k-tile
+
+  char* const L = reinterpret_cast<char*>(lds);
+  const uint32_t lbase =
+      static_cast<uint32_t>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) char*)L));
+  const int KS = (g.K + 15) / 16;
+  const uint32_t abytes = static_cast<uint32_t>(KS * g.M * 32);
+  u32x4 ra = rsrc_words(g.A, abytes);
+  // A: wave w loads token blocks 2w and 2w+1 (32 tokens each) of each k-step
+  uint32_t aoff[2];
+#pragma unroll
+  for (int u = 0; u < 2; ++u)
+    aoff[u] = static_cast<uint32_t>(min(m0 + wave * 64 + u * 32 + lane % 32, g.M - 1) * 32 + (lane / 32) * 16);
+  const uint32_t akstep = static_cast<uint32_t>(g.M) * 32u;
+  // B: wave w loads row blocks 4w..4w+3 (16 rows each); lane l's row and
+  // chunk of the block are what LDS unit l holds
+  u32x4 rb[4];
+  uint32_t boff[4];
+  const int brow = lane / 4, bcol = ((lane % 4) ^ (brow >> 1 & 3) ^ (brow >> 3)) * 8;
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    const int nb0 = n0 + wave * 64 + u * 16;  // the block's first virtual row (uniform)
+    int q, row;
+    if (g.interleave) {
+      q = (nb0 / 64) % 2;
+      row = (nb0 / 128) * 64 + nb0 % 64 + brow;
+    } else {
+      q = nb0 < g.b[1].start || g.nb < 2 ? 0 : (nb0 < g.b[2].start || g.nb < 3 ? 1 : 2);
+      row = nb0 + brow - (q == 0 ? g.b[0].start : (q == 1 ? g.b[1].start : g.b[2].start));
+    }
+    const int64_t ld = q == 0 ? g.b[0].ld : (q == 1 ? g.b[1].ld : g.b[2].ld);
+    const int nrows = q == 0 ? g.b[0].rows : (q == 1 ? g.b[1].rows : g.b[2].rows);
+    const uint16_t* p = q == 0 ? g.b[0].p : (q == 1 ? g.b[1].p : g.b[2].p);
+    rb[u] = rsrc_words(p, static_cast<uint32_t>(nrows * ld * 2));
+    boff[u] = static_cast<uint32_t>(min(row, nrows - 1) * ld * 2) + bcol * 2;
+  }
+  // LDS stage: the A fragments [k-step][token block], then the B blocks. This
+  // wave's part of a k-tile is 8 loads (A and B in turn); sa, sb: the k-tile's
+  // byte offsets in A and in a row of B; la, lb: this wave's places in the stage.
+  uint32_t sa = kt0 * 2 * akstep, sb = kt0 * XBK * 2;
+  const uint32_t la0 = lbase + wave * 2048, lb0 = lbase + XA + wave * 4096;
+  auto target = [&](auto i, uint32_t stage) {
+    constexpr int u = decltype(i)::value / 2;
+    if constexpr (decltype(i)::value % 2 == 0) dma_to<(u / 2 * 8 + u % 2) * 1024>(la0 + stage);
+    else dma_to<u * 1024>(lb0 + stage);
+  };
+  auto load = [&](int i) {
+    const int u = i / 2;
+    if (i % 2 == 0) dma16(ra, aoff[u % 2], u / 2 ? sa + akstep : sa);
+    else dma16(rb[u], boff[u], sb);
+  };
+  // Past the last k-tile the loads go on with empty ranges (no memory
+  // traffic, the stage is not read any more), so the counts stay the same.
+  auto no_more = [&]() {
+    ra.z = 0;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) rb[u].z = 0;
+  };
+  // the partial k-tile (KT - 1), through registers: zeros past K
+  auto stage_tail = [&]() {
+    char* la = L + wave * 2048 + lane * 16;
+    char* lb = L + XA + wave * 4096 + lane * 16;
+    const rsrc_t r = make_rsrc(g.A, abytes);
+    u32x4 va[4], vb[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int ks = (KT - 1) * 2 + u / 2, k = (KT - 1) * XBK + bcol;
+      va[u] = buf_load16(r, ks < KS ? aoff[u % 2] + ks * akstep : kOOB);
+      const uint64_t p = (static_cast<uint64_t>(rb[u].y) << 32) | rb[u].x;
+      vb[u] = buf_load16(make_rsrc(reinterpret_cast<const void*>(p), rb[u].z), k < g.K ? boff[u] + (KT - 1) * XBK * 2 : kOOB);
+      vb[u] = zero_past(vb[u], g.K - k);
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      *reinterpret_cast<u32x4*>(la + (u / 2 * 8 + u % 2) * 1024) = va[u];
+      *reinterpret_cast<u32x4*>(lb + u * 1024) = vb[u];
+    }
+  };
+
+  const int wm = wave / 2, wn = wave % 2;
+  f32x4 acc[8][8];
+#pragma unroll
+  for (int a = 0; a < 8; ++a)
+#pragma unroll
+    for (int b = 0; b < 8; ++b) acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+  // Fragments of 16 rows x 32 k: lane l holds row l % 16, halves 8 (l / 16)..
+  const int br = lane % 16;
+  const int baddr0 = XA + wn * 8192 + (br * 4 + ((lane / 16) ^ (br >> 1 & 3) ^ (br >> 3))) * 16;
+  const int aaddr0 = wm * 4096 + (lane / 32) * (XBM / 32) * 1024 + (lane % 16 + (lane / 16 % 2) * 32) * 16;
+  u32x4 af[2][8], bf[2][8];
+  auto read1 = [&](int i, uint32_t stage, int set) {
+    const char* S = L + stage;
+    if (i < 8) bf[set][i] = *reinterpret_cast<const u32x4*>(S + baddr0 + i * 1024);
+    else af[set][i - 8] = *reinterpret_cast<const u32x4*>(S + aaddr0 + (i - 8) / 2 * 1024 + i % 2 * 256);
+  };
+  // The 64 products of a k-tile. In their shadow the other register set is
+  // read (the next k-tile, from ``stage``) and this wave's loads of a later
+  // k-tile go out to ``into``. One wave has a SIMD to itself, so whatever
+  // stands between two products has to issue within the 16 cycles of the
+  // first: one LDS read, or one load or its target.
+  auto multiply = [&](auto SET, uint32_t stage, uint32_t into) {
+    constexpr int set = decltype(SET)::value;
+    each<64>([&](auto I) {
+      constexpr int i = decltype(I)::value, a = i / 8, b = i % 8;
+      acc[a][b] = mfma16(af[set][a], bf[set][b], acc[a][b]);
+      if constexpr (i < 32 && i % 2 == 0) read1(i / 2, stage, 1 - set);
+      if constexpr (i >= 32 && i % 4 == 0) target(std::integral_constant<int, (i - 32) / 4>{}, into);
+      if constexpr (i >= 32 && i % 4 == 2) load((i - 32) / 4);
+      __builtin_amdgcn_sched_barrier(0);
+    });
+  };
+  // work order: the partial k-tile first, then kt0..; k-tile q of that order
+  // uses stage q % XNST. When q is multiplied, q and q + 1 are in LDS and up
+  // to q + XNST - 1 are on the way: this wave waits for all but its newest
+  // XNST - 3 k-tiles' loads.
+  auto landed = [&]() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(8 * (XNST - 3)) : "memory"); };
+  const int shift = tail ? 1 : 0;
+  int issued = shift;  // k-tiles of the work order issued
+  auto advance = [&]() {
+    sa += 2 * akstep;
+    sb += XBK * 2;
+    if (++issued >= nkt) no_more();
+  };
+  if (tail) stage_tail();
+  if (issued >= nkt) no_more();
+  each<XNST - 1>([&](auto Q) {
+    constexpr int q = decltype(Q)::value;
+    if (q >= shift) {
+      each<8>([&](auto i) {
+        target(i, q * XSTAGE);
+        asm volatile("s_nop 0");
+        load(decltype(i)::value);
+      });
+      advance();
+    }
+  });
+  landed();
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+#pragma unroll
+  for (int i = 0; i < 16; ++i) read1(i, 0, 0);
+  __builtin_amdgcn_sched_barrier(0);
+  uint32_t cur = 0, into = (XNST - 1) * XSTAGE;
+  auto step = [&](auto SET) {
+    const uint32_t next = cur + XSTAGE == XNST * XSTAGE ? 0 : cur + XSTAGE;
+    // everyone is done with k-tile q - 1: its stage takes k-tile q + XNST - 1
+    multiply(SET, next, into);  // past the last k-tile it reads stale values, unused
+    advance();
+    landed();
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    into = cur;
+    cur = next;
+  };
+  // the accumulators are the AGPR half of the registers: without this the
+  // compiler moves some to the other half and spills in the loop
+  auto pin = [&]() {
+#pragma unroll
+    for (int a = 0; a < 8; ++a)
+#pragma unroll
+      for (int b = 0; b < 8; ++b) asm volatile("" : "+a"(acc[a][b]));
+  };
+  pin();
+  for (int q = 0; q < nkt; q += 2) {
+    step(std::integral_constant<int, 0>{});
+    if (q + 1 < nkt) step(std::integral_constant<int, 1>{});
+  }
+  pin();
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+
+  if constexpr (SPLIT) {
+    // as in gemm_kernel: the slices that arrive first park their sums, the
+    // last adds all in slice order
+    unsigned& ticket = *reinterpret_cast<unsigned*>(lds);
+    const int tile = m_tile * g.n_tiles + n_tile;
+    unsigned* arrived = g.cnt + 2 * tile;
+    unsigned* stored = arrived + 1;
+    const int64_t tile_floats = static_cast<int64_t>(XBM) * XBN;
+    auto slot = [&](int sp) {
+      return make_rsrc(g.P + (static_cast<int64_t>(sp) * g.m_tiles * g.n_tiles + tile) * tile_floats,
+                       sp < g.splits ? static_cast<uint32_t>(tile_floats * 4) : 0u);
+    };
+    auto chunk_off = [&](int c) { return static_cast<uint32_t>(((c * XT) + t) * 16); };
+    if (t == 0) ticket = __hip_atomic_fetch_add(arrived, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    if (ticket != static_cast<unsigned>(g.splits - 1)) {
+      const rsrc_t mine = slot(split);
+#pragma unroll
+      for (int c = 0; c < 64; ++c) {
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, acc[c / 8][c % 8]), mine, chunk_off(c), 0, kCoherent);
+      }
+      mem_done();
+      __syncthreads();
+      if (t == 0) __hip_atomic_fetch_add(stored, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      return;
+    }
+    if (t == 0) {
+      unsigned n = 0;
+      while (__hip_atomic_load(stored, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) <
+             static_cast<unsigned>(g.splits - 1)) {
+        __builtin_amdgcn_s_sleep(1);
+        if (++n > kWaitLimit) {  // never expected: report instead of hanging
+          __hip_atomic_fetch_or(g.err, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          break;
+        }
+      }
+    }
+    __syncthreads();
+    rsrc_t sr[MAX_SPLITS];
+#pragma unroll
+    for (int sp = 0; sp < MAX_SPLITS; ++sp) sr[sp] = slot(sp);
+#pragma unroll
+    for (int h = 0; h < 16; ++h) {
+      f32x4 v[4][MAX_SPLITS];
+#pragma unroll
+      for (int c = 0; c < 4; ++c)
+#pragma unroll
+        for (int sp = 0; sp < MAX_SPLITS; ++sp)
+          v[c][sp] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(
+                                                   sr[sp], sp == split ? kOOB : chunk_off(4 * h + c), 0, kCoherent));
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        f32x4& x = acc[h / 2][4 * (h % 2) + c];
+        f32x4 sum = sp_pick(0, split, x, v[c][0]);
+#pragma unroll
+        for (int sp = 1; sp < MAX_SPLITS; ++sp) sum += sp_pick(sp, split, x, v[c][sp]);
+        x = sum;
+      }
+    }
+  }
+
+  wave_epilogue<EPI>(g, acc, L + wave * EPI_WAVE_BYTES, lane, m0 + wm * 128, n0 + wn * 128);
+}
+
+// ---------------------------------------------------------------------------
 // row-wise helpers
 // ---------------------------------------------------------------------------
 constexpr int RT = 256;
@@ -928,9 +1457,10 @@ __global__ void __launch_bounds__(AW * kWave) attn_prefill_kernel(const uint16_t
 // ---------------------------------------------------------------------------
 namespace {
 
-// Split-K choice of a GEMM: the slice count S (whole k-tiles each, at most
-// MAX_SPLITS, the in-kernel reduction's width) with the smallest modelled
-// time. The tiles x S workgroups run in rounds of GEMM_SLOTS (two per compute
+// Tile and split-K choice of a GEMM: the kernel (128 or 256 tile edge) and the
+// slice count S (whole k-tiles each, at most MAX_SPLITS, the in-kernel
+// reduction's width) with the smallest modelled time.
+// 128: the tiles x S workgroups run in rounds of GEMM_SLOTS (two per compute
 // unit); a round in which compute units hold two workgroups advances each by
 // one k-tile per kTwoPerCu microseconds, a last round of at most one per
 // compute unit per kOnePerCu; each of the (S - 1) x tiles fp32 partial tiles
@@ -943,31 +1473,46 @@ namespace {
 // traffic), and at 512 / 1024 / 2048 tokens per chunk 0.222 / 0.340 /
 // 0.609 ms against 0.248 / 0.388 / 0.691 for that rule.
 struct Split {
+  int bm;  // tile edge: 128 (gemm_kernel) or 256 (gemm256_kernel)
   int m_tiles, n_tiles, splits, kps;
 };
 
 constexpr double kTwoPerCu = 1.33, kOnePerCu = 0.75, kPartial = 0.0187;
+// 256: rounds of one workgroup per compute unit, kBig per k-tile and kBigFixed
+// (the first loads, the epilogue) each, and kBigSplit besides the partial
+// tiles if split. Measured on the 7B shapes at 4096 tokens: QKV 204 us (228
+// with the 128 tile), O 87 (98), gate/up 338 (425), down 162 (211); at 1024
+// gate/up 104 (130) but O 66 (39) and down 78 (71); at 256 every GEMM is
+// slower (QKV 54 against 34): few large tiles leave compute units idle.
+constexpr int kBigSlots = 256;
+constexpr double kBig = 1.25, kBigFixed = 27.0, kBigSplit = 15.0, kSmallFixed = 3.0;
 
 Split choose_split(int M, int N, int K) {
-  Split s{};
-  s.m_tiles = (M + pf::GBM - 1) / pf::GBM;
-  s.n_tiles = (N + pf::GBN - 1) / pf::GBN;
   const int KT = std::max(1, (K + pf::GBK - 1) / pf::GBK);
-  const int64_t tiles = std::max(1, s.m_tiles * s.n_tiles);
+  Split s{};
   double best = 0.0;
-  for (int want = 1; want <= std::min(KT, pf::MAX_SPLITS); ++want) {
-    const int kps = (KT + want - 1) / want;
-    const int splits = (KT + kps - 1) / kps;
-    const int64_t groups = tiles * splits;
-    const int64_t full = groups / pf::GEMM_SLOTS, rest = groups % pf::GEMM_SLOTS;
-    double t = static_cast<double>(full) * kps * kTwoPerCu;
-    if (rest > pf::GEMM_SLOTS / 2) t += kps * kTwoPerCu;
-    else if (rest > 0) t += kps * kOnePerCu;
-    t += static_cast<double>(splits - 1) * static_cast<double>(tiles) * kPartial;
-    if (want == 1 || t < best) {
-      best = t;
-      s.kps = kps;
-      s.splits = splits;
+  for (int bm : {pf::GBM, pf::XBM}) {
+    const int m_tiles = (M + bm - 1) / bm, n_tiles = (N + bm - 1) / bm;
+    const int64_t tiles = std::max(1, m_tiles * n_tiles);
+    for (int want = 1; want <= std::min(KT, pf::MAX_SPLITS); ++want) {
+      const int kps = (KT + want - 1) / want;
+      const int splits = (KT + kps - 1) / kps;
+      const int64_t groups = tiles * splits;
+      double t;
+      if (bm == pf::GBM) {
+        const int64_t full = groups / pf::GEMM_SLOTS, rest = groups % pf::GEMM_SLOTS;
+        t = static_cast<double>(full) * kps * kTwoPerCu + kSmallFixed;
+        if (rest > pf::GEMM_SLOTS / 2) t += kps * kTwoPerCu;
+        else if (rest > 0) t += kps * kOnePerCu;
+        t += static_cast<double>(splits - 1) * static_cast<double>(tiles) * kPartial;
+      } else {
+        t = static_cast<double>((groups + kBigSlots - 1) / kBigSlots) * (kps * kBig + kBigFixed);
+        if (splits > 1) t += kBigSplit + static_cast<double>(splits - 1) * static_cast<double>(tiles) * 4 * kPartial;
+      }
+      if (best == 0.0 || t < best) {
+        best = t;
+        s = Split{bm, m_tiles, n_tiles, splits, kps};
+      }
     }
   }
   return s;
@@ -1015,7 +1560,7 @@ PrefillWs prefill_layout(const vt_shard_spec& s, int32_t T) {
   for (int i = 0; i < 4; ++i) {
     const Split sp = choose_split(gm.M, gm.N[i], gm.K[i]);
     const int64_t tiles = static_cast<int64_t>(sp.m_tiles) * sp.n_tiles;
-    if (sp.splits > 1) part = std::max<int64_t>(part, sp.splits * tiles * pf::GBM * pf::GBN * 4);
+    if (sp.splits > 1) part = std::max<int64_t>(part, sp.splits * tiles * sp.bm * sp.bm * 4);
     w.cnt_off[i] = w.ncnt;
     w.ncnt += 2 * static_cast<int>(tiles);  // arrived, stored
   }
@@ -1040,9 +1585,16 @@ PrefillWs prefill_layout(const vt_shard_spec& s, int32_t T) {
 
 // Launches the split-K GEMM with its epilogue; P holds the split-K tiles and
 // cnt the per-tile arrival counters (zero at launch).
+typedef void (*GemmKernel)(pf::GemmArgs);
+constexpr GemmKernel kBigKernels[2][4] = {
+    {pf::gemm256_kernel<pf::EPI_QKV, false>, pf::gemm256_kernel<pf::EPI_O, false>,
+     pf::gemm256_kernel<pf::EPI_GU, false>, pf::gemm256_kernel<pf::EPI_DOWN, false>},
+    {pf::gemm256_kernel<pf::EPI_QKV, true>, pf::gemm256_kernel<pf::EPI_O, true>,
+     pf::gemm256_kernel<pf::EPI_GU, true>, pf::gemm256_kernel<pf::EPI_DOWN, true>}};
+
 vt_status launch_gemm(pf::GemmArgs a, float* P, unsigned* cnt, unsigned* err, hipStream_t s) {
   {
-    // the GEMM's dynamic LDS exceeds the default limit: raise it once per device
+    // the GEMMs' dynamic LDS exceeds the default limit: raise it once per device
     static std::mutex mu;
     static std::vector<char> done;
     int dev = 0;
@@ -1053,6 +1605,11 @@ vt_status launch_gemm(pf::GemmArgs a, float* P, unsigned* cnt, unsigned* err, hi
     if (!done[dev]) {
       e = hipFuncSetAttribute(reinterpret_cast<const void*>(pf::gemm_kernel),
                               hipFuncAttributeMaxDynamicSharedMemorySize, pf::GEMM_LDS_BYTES);
+      for (auto& row : kBigKernels)
+        for (GemmKernel k : row)
+          if (e == hipSuccess)
+            e = hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                    pf::XGEMM_LDS_BYTES);
       if (e != hipSuccess)
         return fail(VT_ERR_HIP, "gemm LDS attribute: %s", hipGetErrorString(e));
       done[dev] = 1;
@@ -1069,8 +1626,11 @@ vt_status launch_gemm(pf::GemmArgs a, float* P, unsigned* cnt, unsigned* err, hi
   if (a.M == 0 || a.N == 0) return VT_OK;
   const int units = sp.n_tiles * sp.splits;
   const int groups = (units + 7) / 8;
-  hipLaunchKernelGGL(pf::gemm_kernel, dim3(groups * 8 * sp.m_tiles), dim3(pf::GT),
-                     pf::GEMM_LDS_BYTES, s, a);
+  const dim3 grid(groups * 8 * sp.m_tiles);
+  if (sp.bm == pf::XBM)
+    hipLaunchKernelGGL(kBigKernels[sp.splits > 1][a.epi], grid, dim3(pf::XT), pf::XGEMM_LDS_BYTES, s, a);
+  else
+    hipLaunchKernelGGL(pf::gemm_kernel, grid, dim3(pf::GT), pf::GEMM_LDS_BYTES, s, a);
   hipError_t e = hipGetLastError();
   return e == hipSuccess ? VT_OK : fail(VT_ERR_HIP, "gemm launch: %s", hipGetErrorString(e));
 }
@@ -1221,6 +1781,7 @@ extern "C" vt_status vt_layer_prefill_chunk(const vt_shard_spec* spec, const vt_
       o.gain = static_cast<const uint16_t*>(w->g_ffn);
       o.U = U;
       o.rowsq = rowsq;
+      o.rowsq_tiles = static_cast<int>((H + pf::GBN - 1) / pf::GBN);
     }
     if ((st = launch_gemm(o, P, cnt + L.cnt_off[1], err, s)) != VT_OK) return st;
   }

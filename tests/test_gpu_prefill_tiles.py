@@ -1,0 +1,135 @@
+"""The prefill GEMMs' 256 x 256 tiles and the long-chunk attention, at the
+shapes where their edges lie: last token tile of one to all rows, hidden sizes
+and column counts that end inside a k-tile and inside an output tile, one and
+several split-K slices. The reference is the layer in float64 (plain torch on
+the same device); bars as in the oracle's prefill tests.
+"""
+import math
+
+import pytest
+import torch
+
+from paper_2607_07046_amd import pack
+from paper_2607_07046_amd import voltron as vt
+from tests.common import FLOOR, NORM_TOL, REL_TOL
+
+pytestmark = pytest.mark.gpu
+BOTH = vt.VT_ATTN | vt.VT_FFN
+EPS, BASE = 1e-5, 10000.0
+
+
+def _normal(g, shape, sigma, mean=0.0):
+    return torch.empty(shape, dtype=torch.float16, device="cuda").normal_(mean, sigma, generator=g)
+
+
+def _rotate(v, pos0):
+    T, _, d = v.shape
+    i = torch.arange(d // 2, dtype=torch.float64, device=v.device)
+    a = torch.arange(pos0, pos0 + T, dtype=torch.float64, device=v.device)[:, None] * BASE ** (-2.0 * i / d)
+    c, s = torch.cos(a)[:, None], torch.sin(a)[:, None]
+    e, o = v[..., 0::2], v[..., 1::2]
+    return torch.stack((e * c - o * s, e * s + o * c), -1).reshape(v.shape)
+
+
+def _rms(x, g):
+    return x / torch.sqrt((x * x).mean(-1, keepdim=True) + EPS) * g.double()
+
+
+def _layer(w, kc, vc, x, pa, pf, heads, kv, d, F, pos, window, h_dev):
+    """h_dev: the h the FFN reads, as the boundary defines it (fp16)."""
+    T = x.shape[0]
+    u = _rms(x.double(), w["g_attn"])
+    q = _rotate((u @ w["wq"].double().T).reshape(T, heads, d), pos)
+    k = _rotate((u @ w["wk"].double().T).reshape(T, kv, d), pos)
+    v = (u @ w["wv"].double().T).reshape(T, kv, d)
+    tok = torch.arange(pos, pos + T, device=x.device)[:, None]
+    key = torch.arange(pos + T, device=x.device)[None]
+    hidden = key > tok
+    if window:
+        hidden |= key <= tok - window
+    o = torch.empty((T, heads, d), dtype=torch.float64, device=x.device)
+    for j in range(heads):
+        g = j // (heads // kv)
+        K, V = torch.cat((kc[g, :pos].double(), k[:, g])), torch.cat((vc[g, :pos].double(), v[:, g]))
+        sc = (q[:, j] @ K.T / math.sqrt(d)).masked_fill_(hidden, -math.inf)
+        o[:, j] = torch.softmax(sc, -1) @ V
+    p = o.reshape(T, -1) @ w["wo"].double().T
+    h = x.double() + p + pa.double()
+    u = _rms(h_dev.double(), w["g_ffn"])
+    gate = u @ w["wg"].double().T
+    f = (gate * torch.sigmoid(gate) * (u @ w["wu"].double().T)) @ w["wd"][:, :F].double().T
+    return {"p_attn": p, "h": h, "p_ffn": f, "y": h_dev.double() + f + pf.double(), "k": k.transpose(0, 1),
+            "v": v.transpose(0, 1)}
+
+
+def _close(got, ref, what):
+    got = got.double()
+    assert torch.isfinite(got).all(), what
+    err = (got - ref).abs()
+    floor = FLOOR * ref.square().mean(-1, keepdim=True).sqrt()  # of the row: rows differ in size
+    rel = float((err / torch.maximum(ref.abs(), floor)).max())
+    norm = float(err.norm() / ref.norm())
+    print(f"[tiles] {what}: element-wise {rel:.4f}, normwise {norm:.6f}")
+    assert rel <= REL_TOL and norm <= NORM_TOL, (what, rel, norm)
+
+
+def run_layer(T, hidden, heads, kv, d, F, ctx, window=0, seed=0):
+    g = torch.Generator(device="cuda").manual_seed(100 + seed)
+    dims = vt.vt_layer_dims(hidden=hidden, n_heads=heads, n_kv_heads=kv, head_dim=d, ffn=F, rms_eps=EPS,
+                            rope_base=BASE, window=window)
+    spec = vt.vt_shard_spec_create(dims, [1.0], [1.0], 0)
+    dims, info = vt.vt_shard_spec_query(spec)
+    s = 1.0 / math.sqrt(hidden)
+    ld = pack.round_up(F, 8)
+    w = {"g_attn": _normal(g, (hidden,), 0.1, 1.0), "g_ffn": _normal(g, (hidden,), 0.1, 1.0),
+         "wq": _normal(g, (heads * d, hidden), s), "wk": _normal(g, (kv * d, hidden), s),
+         "wv": _normal(g, (kv * d, hidden), s), "wo": _normal(g, (hidden, heads * d), s),
+         "wg": _normal(g, (F, hidden), s), "wu": _normal(g, (F, hidden), s)}
+    w["wd"] = torch.full((hidden, ld), math.nan, dtype=torch.float16, device="cuda")  # row padding: never read
+    w["wd"][:, :F] = _normal(g, (hidden, F), s)
+    cap = ctx + T + 2
+    kc, vc = _normal(g, (kv, cap, d), 1.0), _normal(g, (kv, cap, d), 1.0)
+    k0, v0 = kc.clone(), vc.clone()
+    x, pa, pf = (_normal(g, (T, hidden), 1.0) for _ in range(3))
+    out = {n: torch.full((T + 1, hidden), 7.0, dtype=torch.float16, device="cuda")
+           for n in ("p_attn", "h", "p_ffn", "y")}
+    ws = torch.zeros(vt.vt_workspace_size(spec, T, cap), dtype=torch.uint8, device="cuda")
+    io = vt.vt_layer_io(x=x.data_ptr(), peer_attn=pa.data_ptr(), peer_ffn=pf.data_ptr(),
+                        attn_partial=out["p_attn"].data_ptr(), h=out["h"].data_ptr(),
+                        ffn_partial=out["p_ffn"].data_ptr(), y=out["y"].data_ptr())
+    view = vt.vt_kv_view(k=kc.data_ptr(), v=vc.data_ptr(), capacity=cap, n_kv_heads=kv, head_dim=d, len=ctx)
+    vt.vt_layer_prefill_chunk(spec, pack.struct_of(w, dims, info, ld), view, io, T, ctx, BOTH, ws.data_ptr(),
+                              ws.numel(), torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    assert int(ws[vt.VT_WS_ERROR_WORD:vt.VT_WS_ERROR_WORD + 4].view(torch.int32)) == 0
+    ref = _layer(w, k0, v0, x, pa, pf, heads, kv, d, F, ctx, window, out["h"][:T])
+    for n in ("p_attn", "h", "p_ffn", "y"):
+        assert (out[n][T] == 7.0).all(), n  # nothing past the chunk's rows
+        _close(out[n][:T], ref[n], n)
+    _close(kc[:, ctx:ctx + T], ref["k"], "keys")
+    _close(vc[:, ctx:ctx + T], ref["v"], "values")
+    for c, c0 in ((kc, k0), (vc, v0)):
+        assert torch.equal(c[:, :ctx], c0[:, :ctx]) and torch.equal(c[:, ctx + T:], c0[:, ctx + T:])
+    return out
+
+
+# tokens, hidden, heads, KV heads, head_dim, FFN columns, context
+GEMM_EDGES = [
+    (2305, 4104, 24, 24, 64, 4099, 5),     # QKV, gate/up, down unsplit; K ends 8 and 3 into a k-tile
+    (777, 8192, 24, 3, 128, 10609, 130),   # gate/up and down in 2 slices, the second with the partial k-tile
+    (4090, 4096, 16, 16, 128, 1031, 0),    # O unsplit
+    (900, 8192, 64, 8, 128, 520, 33),      # O in 2 slices
+]
+
+
+@pytest.mark.parametrize("shape", GEMM_EDGES, ids=[f"T{s[0]}-H{s[1]}-F{s[5]}" for s in GEMM_EDGES])
+def test_gemm_tile_edges(shape):
+    run_layer(*shape)
+
+
+def test_gemm_split_repeat_is_bitwise():
+    """The slices' sums are added in slice order, whichever arrives last."""
+    a = run_layer(*GEMM_EDGES[1])
+    b = run_layer(*GEMM_EDGES[1])
+    for n in a:
+        assert torch.equal(a[n], b[n]), n
