@@ -1450,6 +1450,221 @@ __global__ void __launch_bounds__(AW * kWave) attn_prefill_kernel(const uint16_t
   }
 }
 
+// ---------------------------------------------------------------------------
+// The same attention for longer chunks: keys and values shared by 128 queries.
+//
+// In attn_prefill_kernel every 32 queries fetch and stage all keys and values
+// themselves: 16 KiB through L1 (256 cycles) and 40 KiB through LDS (320 cycles)
+// per 32 x 32 block with 512 cycles of MFMA on one of four SIMDs. Here a
+// workgroup takes 128 queries of a head, four waves of 32, whose Q stays in
+// registers; key blocks of 32 go from memory straight into a ring of LQST
+// LDS stages that the four waves share (4 KiB and 20 KiB per 32 x 32 block). Two
+// such groups of four waves take every second key block and merge at the end:
+// two waves per SIMD, one's softmax behind the other's MFMAs. The 7B 50%
+// shard's attention takes 155 us at 4096 tokens (254 before), 72 at 2048 (98).
+//
+// LDS rows of D halves: the 16-byte chunk c of row r is at c ^ (r % 16) for K
+// (r % 8 for 64 dimensions), whose fragments take one chunk of 32 rows, and at
+// c ^ 2 (r % 8) (r % 4) for V, whose transposing reads take two chunks of four
+// rows. K rows are permuted as in attn_prefill_kernel. Keys past the last one
+// the workgroup attends read that one instead (and are masked).
+// The sums of probabilities stay per lane until the end; exp(s - m) is one fma
+// and one exp2.
+// ---------------------------------------------------------------------------
+constexpr int LQ = 128, LQST = 4, KW = 2, LT = 256 * KW;
+
+template <int D>
+__global__ void __launch_bounds__(LT, 2) attn_long_kernel(const uint16_t* Q, uint16_t* O, const uint16_t* kc,
+                                                                const uint16_t* vc, int T, int nq, int G, int cap,
+                                                                int pos0, int window) {
+  extern __shared__ __attribute__((aligned(16))) uint16_t lds[];
+  constexpr int NKS = D / 16, CPR = D / 8;       // k-steps over D; 16-byte chunks per row
+  constexpr int RPB = 64 / CPR;                  // rows of 1 KiB
+  constexpr int TILE = KB * D * 2;               // bytes of a K (or V) block
+  constexpr int STAGE = 2 * KW * TILE;
+  constexpr int LPW = TILE / 1024 / 4;           // K (and V) loads per wave and block
+  const int lane = threadIdx.x % kWave;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int qg = wave % 4, kw = wave / 4;
+  // equal index mod 8 (one XCD) for all query blocks of a head; the blocks
+  // with the most keys first
+  const int nh = (nq + 7) / 8 * 8, nqb = (T + LQ - 1) / LQ;
+  const int j = blockIdx.x % nh, qb = nqb - 1 - blockIdx.x / nh;
+  if (j >= nq) return;
+  const int g = j / G;
+  const int t0 = qb * LQ, w0 = t0 + qg * 32;     // the workgroup's and the wave's first query
+  const int tq = w0 + lane % 32, qpos = pos0 + tq;
+
+  char* const L = reinterpret_cast<char*>(lds);
+  const uint32_t lbase =
+      static_cast<uint32_t>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) char*)L));
+  const int last_key = pos0 + min(t0 + LQ, T) - 1;
+  const int wave_last = pos0 + min(w0 + 32, T) - 1;  // below pos0 + w0 if the wave has no query
+  const int kb0 = window > 0 ? max(0, pos0 + t0 - window + 1) / KB : 0;
+  const int nit = (last_key / KB + 1 - kb0 + KW - 1) / KW;
+  const uint32_t range = static_cast<uint32_t>(last_key + 1) * D * 2u;
+  const u32x4 rk = rsrc_words(kc + static_cast<int64_t>(g) * cap * D, range);
+  const u32x4 rv = rsrc_words(vc + static_cast<int64_t>(g) * cap * D, range);
+  // this wave's loads of its group's block: rows qg * LPW * RPB .., LPW x 1 KiB
+  int krow[LPW], vrow[LPW];
+  uint32_t kcol[LPW], vcol[LPW];
+#pragma unroll
+  for (int u = 0; u < LPW; ++u) {
+    const int r = (qg * LPW + u) * RPB + lane / CPR, c = lane % CPR;
+    krow[u] = swap_bits23(r);
+    kcol[u] = static_cast<uint32_t>((c ^ (r % CPR)) * 16);
+    vrow[u] = r;
+    vcol[u] = static_cast<uint32_t>((c ^ (2 * (r % (CPR / 2)))) * 16);
+  }
+  auto issue = [&](int it, uint32_t stage) {
+    const int p0 = (kb0 + it * KW + kw) * KB;
+    const uint32_t base = lbase + stage + kw * 2 * TILE + qg * LPW * 1024;
+#pragma unroll
+    for (int u = 0; u < LPW; ++u) {
+      dma_to<0>(base + u * 1024);
+      asm volatile("s_nop 0");
+      dma16(rk, static_cast<uint32_t>(min(p0 + krow[u], last_key)) * (D * 2u) + kcol[u], 0);
+      dma_to<TILE>(base + u * 1024);
+      asm volatile("s_nop 0");
+      dma16(rv, static_cast<uint32_t>(min(p0 + vrow[u], last_key)) * (D * 2u) + vcol[u], 0);
+    }
+  };
+#pragma unroll
+  for (int q = 0; q < LQST - 1; ++q) issue(q, q * STAGE);  // past the end: the last key's row again
+
+  u32x4 qf[NKS];
+#pragma unroll
+  for (int ks = 0; ks < NKS; ++ks)
+    qf[ks] = load16(Q + (static_cast<int64_t>(min(tq, T - 1)) * nq + j) * D + ks * 16 + 8 * (lane / 32));
+  f32x16 o[D / 32];
+#pragma unroll
+  for (int mt = 0; mt < D / 32; ++mt) o[mt] = f32x16{};
+  float mrun = -INFINITY, lrun = 0.f;
+  constexpr float kLog2e = 1.44269504088896340736f;
+
+  const int kr = lane % 32;
+  const int kaddr = kw * 2 * TILE + kr * D * 2, kx = kr % CPR;
+  // V: lane's key row (of 4 consecutive ones) and 8-byte piece of a 16-dimension group
+  const int grp = lane / 16, jl = lane % 16;
+  const int vkey = 8 * (grp / 2) + jl / 4, vdim = 2 * (grp % 2) + (jl % 4) / 2;
+  // the Q loads are waited for here: a wait inside the loop would also be one
+  // for the blocks on their way
+#pragma unroll
+  for (int ks = 0; ks < NKS; ++ks) asm volatile("" : "+v"(qf[ks]));
+  uint32_t cur = 0, into = (LQST - 1) * STAGE;
+  for (int it = 0; it < nit; ++it) {
+    // all but the newest LQST - 2 blocks' loads have landed, here and, after
+    // the barrier, everywhere; the previous block's stage is free
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * LPW * (LQST - 2)) : "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    issue(it + LQST - 1, into);
+    const char* S = L + cur;
+    into = cur;
+    cur = cur + STAGE == LQST * STAGE ? 0 : cur + STAGE;
+    const int p0 = (kb0 + it * KW + kw) * KB;
+    // nothing of the block is attended by this wave's queries
+    if (w0 >= T || p0 > wave_last || (window > 0 && p0 + KB - 1 <= pos0 + w0 - window)) continue;
+    // the block's fragments, all on their way before the first is used: V's
+    // arrive behind the scores
+    u32x4 kf[NKS];
+#pragma unroll
+    for (int ks = 0; ks < NKS; ++ks)
+      kf[ks] = *reinterpret_cast<const u32x4*>(S + kaddr + ((2 * ks + lane / 32) ^ kx) * 16);
+    v4h16 vf[D / 32][2][2];
+#pragma unroll
+    for (int mt = 0; mt < D / 32; ++mt)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int r = q / 2 * 16 + vkey + q % 2 * 4;
+        vf[mt][q / 2][q % 2] = lds_read_tr16(reinterpret_cast<const uint16_t*>(
+            S + kw * 2 * TILE + TILE + r * D * 2 + ((4 * mt + vdim) ^ (2 * (r % (CPR / 2)))) * 16 + (jl % 2) * 8));
+      }
+    __builtin_amdgcn_sched_barrier(0);
+    f32x16 s = f32x16{};
+#pragma unroll
+    for (int ks = 0; ks < NKS; ++ks) s = mfma32(kf[ks], qf[ks], s);
+    const bool masked = p0 + KB - 1 > pos0 + w0 || w0 + 32 > T || (window > 0 && p0 <= pos0 + w0 + 31 - window);
+    if (masked) {
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        const int key = p0 + swap_bits23(8 * (i / 4) + 4 * (lane / 32) + i % 4);
+        if (key > qpos || tq >= T || (window > 0 && key <= qpos - window)) s[i] = -INFINITY;
+      }
+    }
+    float bm = s[0];
+#pragma unroll
+    for (int i = 1; i < 16; ++i) bm = fmaxf(bm, s[i]);
+    bm = fmaxf(bm, __shfl_xor(bm, 32, kWave));
+    const float mnew = fmaxf(mrun, bm);
+    // a query that has seen no key yet keeps a zero reference: exp2(-inf) = 0
+    const float ml = mnew == -INFINITY ? 0.f : mnew * kLog2e;
+    if (__builtin_amdgcn_ballot_w64(mnew != mrun) != 0) {
+      const float alpha = __builtin_amdgcn_exp2f(fmaf(mrun, kLog2e, -ml));
+      lrun *= alpha;
+#pragma unroll
+      for (int mt = 0; mt < D / 32; ++mt)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) o[mt][i] *= alpha;
+      mrun = mnew;
+    }
+    u32x4 pf[2];
+#pragma unroll
+    for (int s2 = 0; s2 < 2; ++s2) {
+      uint16_t h[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const float pe = __builtin_amdgcn_exp2f(fmaf(s[8 * s2 + e], kLog2e, -ml));
+        lrun += pe;
+        h[e] = f2h(pe);
+      }
+      pf[s2] = pack8(h);
+    }
+#pragma unroll
+    for (int mt = 0; mt < D / 32; ++mt)
+#pragma unroll
+      for (int s2 = 0; s2 < 2; ++s2) o[mt] = mfma32(pack_v4(vf[mt][s2][0], vf[mt][s2][1]), pf[s2], o[mt]);
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  lrun += __shfl_xor(lrun, 32, kWave);
+
+  // group 1's waves leave their sums in LDS, in register order, for group 0's
+  float* part = reinterpret_cast<float*>(lds) + qg * (D / 2 + 2) * kWave + lane;
+  if (kw == 1) {
+#pragma unroll
+    for (int mt = 0; mt < D / 32; ++mt)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) part[(mt * 16 + i) * kWave] = o[mt][i];
+    part[(D / 2) * kWave] = mrun;
+    part[(D / 2 + 1) * kWave] = lrun;
+  }
+  __syncthreads();
+  if (kw == 1) return;
+  const float m1 = part[(D / 2) * kWave], l1 = part[(D / 2 + 1) * kWave];
+  const float ms = fmaxf(mrun, m1), ml = ms == -INFINITY ? 0.f : ms * kLog2e;
+  const float a0 = __builtin_amdgcn_exp2f(fmaf(mrun, kLog2e, -ml));
+  const float a1 = __builtin_amdgcn_exp2f(fmaf(m1, kLog2e, -ml));
+  lrun = lrun * a0 + l1 * a1;
+#pragma unroll
+  for (int mt = 0; mt < D / 32; ++mt)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) o[mt][i] = o[mt][i] * a0 + part[(mt * 16 + i) * kWave] * a1;
+  if (tq >= T) return;
+  // O^T accumulator i of tile mt: dim 32 mt + 8(i/4) + 4(l/32) + i%4
+  const float inv = 1.0f / lrun;
+#pragma unroll
+  for (int mt = 0; mt < D / 32; ++mt)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      uint16_t h[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) h[e] = f2h(o[mt][4 * q + e] * inv);
+      *reinterpret_cast<uint2*>(O + kmajor(j * D + 32 * mt + 8 * q + 4 * (lane / 32), tq, T)) =
+          make_uint2(h[0] | (static_cast<unsigned>(h[1]) << 16), h[2] | (static_cast<unsigned>(h[3]) << 16));
+    }
+}
+
 }  // namespace pf
 
 // ---------------------------------------------------------------------------
@@ -1583,8 +1798,22 @@ PrefillWs prefill_layout(const vt_shard_spec& s, int32_t T) {
   return w;
 }
 
-// Launches the split-K GEMM with its epilogue; P holds the split-K tiles and
-// cnt the per-tile arrival counters (zero at launch).
+// A kernel whose dynamic LDS exceeds the default limit: raise it once per
+// device (``done``: the devices it has been raised on).
+vt_status raise_lds(const void* kernel, int bytes, std::mutex& mu, std::vector<char>& done) {
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return fail(VT_ERR_HIP, "hipGetDevice: %s", hipGetErrorString(e));
+  std::lock_guard<std::mutex> lk(mu);
+  if (static_cast<int>(done.size()) <= dev) done.resize(dev + 1, 0);
+  if (!done[dev]) {
+    e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+    if (e != hipSuccess) return fail(VT_ERR_HIP, "LDS attribute: %s", hipGetErrorString(e));
+    done[dev] = 1;
+  }
+  return VT_OK;
+}
+
 typedef void (*GemmKernel)(pf::GemmArgs);
 constexpr GemmKernel kBigKernels[2][4] = {
     {pf::gemm256_kernel<pf::EPI_QKV, false>, pf::gemm256_kernel<pf::EPI_O, false>,
@@ -1592,29 +1821,9 @@ constexpr GemmKernel kBigKernels[2][4] = {
     {pf::gemm256_kernel<pf::EPI_QKV, true>, pf::gemm256_kernel<pf::EPI_O, true>,
      pf::gemm256_kernel<pf::EPI_GU, true>, pf::gemm256_kernel<pf::EPI_DOWN, true>}};
 
+// Launches the split-K GEMM with its epilogue; P holds the split-K tiles and
+// cnt the per-tile arrival counters (zero at launch).
 vt_status launch_gemm(pf::GemmArgs a, float* P, unsigned* cnt, unsigned* err, hipStream_t s) {
-  {
-    // the GEMMs' dynamic LDS exceeds the default limit: raise it once per device
-    static std::mutex mu;
-    static std::vector<char> done;
-    int dev = 0;
-    hipError_t e = hipGetDevice(&dev);
-    if (e != hipSuccess) return fail(VT_ERR_HIP, "hipGetDevice: %s", hipGetErrorString(e));
-    std::lock_guard<std::mutex> lk(mu);
-    if (static_cast<int>(done.size()) <= dev) done.resize(dev + 1, 0);
-    if (!done[dev]) {
-      e = hipFuncSetAttribute(reinterpret_cast<const void*>(pf::gemm_kernel),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, pf::GEMM_LDS_BYTES);
-      for (auto& row : kBigKernels)
-        for (GemmKernel k : row)
-          if (e == hipSuccess)
-            e = hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                    pf::XGEMM_LDS_BYTES);
-      if (e != hipSuccess)
-        return fail(VT_ERR_HIP, "gemm LDS attribute: %s", hipGetErrorString(e));
-      done[dev] = 1;
-    }
-  }
   const Split sp = choose_split(a.M, a.N, a.K);
   a.m_tiles = sp.m_tiles;
   a.n_tiles = sp.n_tiles;
@@ -1627,12 +1836,55 @@ vt_status launch_gemm(pf::GemmArgs a, float* P, unsigned* cnt, unsigned* err, hi
   const int units = sp.n_tiles * sp.splits;
   const int groups = (units + 7) / 8;
   const dim3 grid(groups * 8 * sp.m_tiles);
-  if (sp.bm == pf::XBM)
-    hipLaunchKernelGGL(kBigKernels[sp.splits > 1][a.epi], grid, dim3(pf::XT), pf::XGEMM_LDS_BYTES, s, a);
+  const bool big = sp.bm == pf::XBM;
+  const GemmKernel kernel = big ? kBigKernels[sp.splits > 1][a.epi] : pf::gemm_kernel;
+  static std::mutex mu;
+  static std::vector<char> raised[9];  // per kernel
+  if (vt_status st = raise_lds(reinterpret_cast<const void*>(kernel), big ? pf::XGEMM_LDS_BYTES : pf::GEMM_LDS_BYTES, mu,
+                               raised[big ? 1 + 4 * (sp.splits > 1) + a.epi : 0]);
+      st != VT_OK)
+    return st;
+  if (big)
+    hipLaunchKernelGGL(kernel, grid, dim3(pf::XT), pf::XGEMM_LDS_BYTES, s, a);
   else
-    hipLaunchKernelGGL(pf::gemm_kernel, grid, dim3(pf::GT), pf::GEMM_LDS_BYTES, s, a);
+    hipLaunchKernelGGL(kernel, grid, dim3(pf::GT), pf::GEMM_LDS_BYTES, s, a);
   hipError_t e = hipGetLastError();
   return e == hipSuccess ? VT_OK : fail(VT_ERR_HIP, "gemm launch: %s", hipGetErrorString(e));
+}
+
+// Workgroups of 128 queries from which attn_long_kernel is the faster one.
+// Measured at 16 heads of 128 dimensions, positions 768..: 64 workgroups (512
+// tokens) 34.5 us against 20.6 for attn_prefill_kernel, 128 (1024) 47 against 45,
+// 256 (2048) 72 against 98, 512 (4096) 155 against 254; at 24 heads,
+// positions 2049..: 168 (777) 80 against 82. Below, whole compute units idle.
+constexpr int kLongGroups = 160;
+
+template <int D>
+vt_status launch_attention_d(const uint16_t* Q, uint16_t* O, const vt_kv_view& kv, int T, int nq, int G, int pos0,
+                             int window, hipStream_t s) {
+  const uint16_t* kc = static_cast<const uint16_t*>(kv.k);
+  const uint16_t* vc = static_cast<const uint16_t*>(kv.v);
+  const int heads8 = (nq + 7) / 8 * 8, qblocks = (T + pf::LQ - 1) / pf::LQ;
+  if (static_cast<int64_t>(nq) * qblocks >= kLongGroups) {
+    constexpr int lds = pf::LQST * 2 * pf::KW * pf::KB * D * 2;
+    static std::mutex mu;
+    static std::vector<char> raised;
+    if (vt_status st = raise_lds(reinterpret_cast<const void*>(pf::attn_long_kernel<D>), lds, mu, raised); st != VT_OK)
+      return st;
+    hipLaunchKernelGGL(pf::attn_long_kernel<D>, dim3(heads8 * qblocks), dim3(pf::LT), lds, s, Q, O, kc, vc, T, nq, G,
+                       kv.capacity, pos0, window);
+  } else {
+    hipLaunchKernelGGL(pf::attn_prefill_kernel<D>, dim3(heads8 * ((T + pf::QB - 1) / pf::QB)), dim3(pf::AW * kWave), 0,
+                       s, Q, O, kc, vc, T, nq, G, kv.capacity, pos0, window);
+  }
+  const hipError_t e = hipGetLastError();
+  return e == hipSuccess ? VT_OK : fail(VT_ERR_HIP, "attention launch: %s", hipGetErrorString(e));
+}
+
+vt_status launch_attention(const uint16_t* Q, uint16_t* O, const vt_kv_view& kv, int T, int nq, int G, int d, int pos0,
+                           int window, hipStream_t s) {
+  return d == 128 ? launch_attention_d<128>(Q, O, kv, T, nq, G, pos0, window, s)
+                  : launch_attention_d<64>(Q, O, kv, T, nq, G, pos0, window, s);
 }
 
 pf::BSrc bsrc(const void* p, int64_t ld, int start, int rows) {
@@ -1758,16 +2010,7 @@ extern "C" vt_status vt_layer_prefill_chunk(const vt_shard_spec* spec, const vt_
     a.cap = kv->capacity;
     a.pos0 = pos0;
     if ((st = launch_gemm(a, P, cnt + L.cnt_off[0], err, s)) != VT_OK) return st;
-    const int blocks = (nq + 7) / 8 * 8 * ((n_tok + pf::QB - 1) / pf::QB);
-    if (d == 128)
-      hipLaunchKernelGGL(pf::attn_prefill_kernel<128>, dim3(blocks), dim3(pf::AW * kWave), 0, s, Qr, Ob,
-                         static_cast<const uint16_t*>(kv->k), static_cast<const uint16_t*>(kv->v),
-                         n_tok, nq, G, kv->capacity, pos0, D.window);
-    else
-      hipLaunchKernelGGL(pf::attn_prefill_kernel<64>, dim3(blocks), dim3(pf::AW * kWave), 0, s, Qr, Ob,
-                         static_cast<const uint16_t*>(kv->k), static_cast<const uint16_t*>(kv->v),
-                         n_tok, nq, G, kv->capacity, pos0, D.window);
-    if ((st = check("attention")) != VT_OK) return st;
+    if ((st = launch_attention(Qr, Ob, *kv, n_tok, nq, G, static_cast<int>(d), pos0, D.window, s)) != VT_OK) return st;
     // O; epilogue: h = x + p_attn + peer, and with the FFN to follow its
     // input h * g_ffn and the sums of h^2 its RMSNorm needs
     pf::GemmArgs o = gemm(1, Ob, pf::EPI_O);

@@ -133,3 +133,21 @@ def test_gemm_split_repeat_is_bitwise():
     b = run_layer(*GEMM_EDGES[1])
     for n in a:
         assert torch.equal(a[n], b[n]), n
+
+
+# attention with 128 queries per workgroup: enough heads and tokens for it, the
+# last block of one query and of all, contexts that end inside a key block,
+# fewer keys than queries, sliding windows inside and across blocks, GQA groups
+ATTN_EDGES = [
+    (2561, 512, 8, 8, 64, 64, 0, 0),
+    (641, 512, 32, 8, 128, 64, 31, 0),
+    (1280, 1024, 16, 2, 128, 64, 1000, 0),
+    (1155, 512, 20, 4, 64, 64, 77, 33),
+    (1153, 512, 18, 18, 128, 64, 500, 128),
+    (1030, 512, 20, 20, 64, 64, 7, 1),
+]
+
+
+@pytest.mark.parametrize("shape", ATTN_EDGES, ids=[f"T{s[0]}-q{s[2]}-d{s[4]}-w{s[7]}" for s in ATTN_EDGES])
+def test_long_attention_edges(shape):
+    run_layer(*shape, seed=1)
