@@ -177,3 +177,35 @@ def test_pruned_shards_sum_to_pruned_layer(dropped):
     a, h, f = shards_step(kept, x, wl.ctx)
     assert_close(a, ref["p_attn"], "kept attention partials")
     assert_close(f, ffn_at_h16(Wp, d.rms_eps, ref)["p_ffn"], "kept FFN partials")
+
+
+@pytest.mark.parametrize("F", [40, 1003, 9001, 16395])
+@pytest.mark.parametrize("c0", [1, 2, 5, 7, 8, 11])
+def test_shard_pack_column_offsets(F, c0):
+    """Wd's columns from every kind of offset within a 16-byte chunk, with
+    several rows to a workgroup, one, and several workgroups to a row (1024
+    chunks of 8 columns each); the source's row padding is never read into
+    the result, the result's is zero."""
+    H = 64
+    dims = vt.vt_layer_dims(hidden=H, n_heads=2, n_kv_heads=2, head_dim=64, ffn=F, rms_eps=1e-5, rope_base=1e4,
+                            window=0)
+    spec = vt.vt_shard_spec_create(dims, [0.5, 0.5], [c0 / F, 1.0 - c0 / F], 1)
+    dims, info = vt.vt_shard_spec_query(spec)
+    assert info.col_begin == c0 and info.n_cols == F - c0
+    g = torch.Generator(device="cuda").manual_seed(F + c0)
+    normal = lambda *shape: torch.empty(shape, dtype=torch.float16, device="cuda").normal_(generator=g)
+    ld = pack.round_up(F, 8)
+    full = {"g_attn": normal(H), "g_ffn": normal(H), "wq": normal(128, H), "wk": normal(128, H),
+            "wv": normal(128, H), "wo": normal(H, 128), "wg": normal(F, H), "wu": normal(F, H),
+            "wd": torch.full((H, ld), 9.0, dtype=torch.float16, device="cuda")}
+    full["wd"][:, :F] = normal(H, F)
+    whole = vt.vt_shard_info(0, 2, 0, 2, 0, F)
+    new = pack.alloc_shard(dims, info)
+    for t in new.tensors.values():
+        t.fill_(7.0)
+    vt.vt_shard_pack(spec, pack.struct_of(full, dims, whole, ld), new.struct, torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    n = F - c0
+    assert torch.equal(new.tensors["wd"][:, :n], full["wd"][:, c0:F])
+    assert not new.tensors["wd"][:, n:pack.round_up(n, 8)].any()
+    assert torch.equal(new.tensors["wg"][:n], full["wg"][c0:]) and torch.equal(new.tensors["wo"], full["wo"][:, 64:])
