@@ -1468,8 +1468,9 @@ __global__ void __launch_bounds__(AW * kWave) attn_prefill_kernel(const uint16_t
 // c ^ 2 (r % 8) (r % 4) for V, whose transposing reads take two chunks of four
 // rows. K rows are permuted as in attn_prefill_kernel. Keys past the last one
 // the workgroup attends read that one instead (and are masked).
-// The sums of probabilities stay per lane until the end; exp(s - m) is one fma
-// and one exp2.
+// The sums of probabilities stay per lane until the end and are of the values
+// as rounded for the second product, so that a rounding moves numerator and
+// denominator together; exp(s - m) is one fma and one exp2.
 // ---------------------------------------------------------------------------
 constexpr int LQ = 128, LQST = 4, KW = 2, LT = 256 * KW;
 
@@ -1614,9 +1615,8 @@ __global__ void __launch_bounds__(LT, 2) attn_long_kernel(const uint16_t* Q, uin
       uint16_t h[8];
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
-        const float pe = __builtin_amdgcn_exp2f(fmaf(s[8 * s2 + e], kLog2e, -ml));
-        lrun += pe;
-        h[e] = f2h(pe);
+        h[e] = f2h(__builtin_amdgcn_exp2f(fmaf(s[8 * s2 + e], kLog2e, -ml)));
+        lrun += h2f(h[e]);
       }
       pf[s2] = pack8(h);
     }
