@@ -1856,8 +1856,9 @@ vt_status launch_gemm(pf::GemmArgs a, float* P, unsigned* cnt, unsigned* err, hi
 // Measured at 16 heads of 128 dimensions, positions 768..: 64 workgroups (512
 // tokens) 34.5 us against 20.6 for attn_prefill_kernel, 128 (1024) 47 against 45,
 // 256 (2048) 72 against 98, 512 (4096) 155 against 254; at 24 heads,
-// positions 2049..: 168 (777) 80 against 82. Below, whole compute units idle.
-constexpr int kLongGroups = 160;
+// positions 2049..: 168 (777) 80 against 82, no gain worth another summation.
+// Below, whole compute units idle.
+constexpr int kLongGroups = 224;
 
 template <int D>
 vt_status launch_attention_d(const uint16_t* Q, uint16_t* O, const vt_kv_view& kv, int T, int nq, int G, int pos0,

@@ -139,12 +139,13 @@ def test_gemm_split_repeat_is_bitwise():
 # last block of one query and of all, contexts that end inside a key block,
 # fewer keys than queries, sliding windows inside and across blocks, GQA groups
 ATTN_EDGES = [
-    (2561, 512, 8, 8, 64, 64, 0, 0),
-    (641, 512, 32, 8, 128, 64, 31, 0),
-    (1280, 1024, 16, 2, 128, 64, 1000, 0),
-    (1155, 512, 20, 4, 64, 64, 77, 33),
-    (1153, 512, 18, 18, 128, 64, 500, 128),
-    (1030, 512, 20, 20, 64, 64, 7, 1),
+    (3585, 512, 8, 8, 64, 64, 0, 0),
+    (897, 512, 32, 8, 128, 64, 31, 0),
+    (1793, 1024, 16, 2, 128, 64, 1000, 0),
+    (1411, 512, 20, 4, 64, 64, 77, 33),
+    (1665, 512, 18, 18, 128, 64, 500, 128),
+    (1542, 512, 20, 20, 64, 64, 7, 1),
+    (1792, 512, 16, 16, 128, 64, 40, 0),
 ]
 
 
