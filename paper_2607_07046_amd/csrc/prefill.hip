@@ -29,6 +29,7 @@
 
 #include "device.hpp"
 #include "internal.hpp"
+#include "prefill_walk.hpp"
 
 namespace vt {
 namespace pf {
@@ -637,11 +638,15 @@ __global__ void __launch_bounds__(GT, 2) gemm_kernel(GemmArgs g) {
 // in different bank groups.
 //
 // Rows past M or N read a valid row instead (their sums are never stored).
+// The k offset is these loads' scalar offset, unlike the other buffer loads',
+// which keep it 0: whether the range check sees it is not relied on, since a
+// lane's row is clamped and whole k-tiles end inside it, and since the empty
+// ranges past the last k-tile come with offset 0 (KWalk).
 // A k-tile that reaches past K (at most one, the slice's first in the order
 // of work) is loaded through registers and masked.
 // ---------------------------------------------------------------------------
 constexpr int XBM = 256, XBN = 256, XT = 256;
-constexpr int XBK = 32, XNST = 5;
+constexpr int XBK = KWalk::kTile, XNST = 5;
 constexpr int XA = XBM * XBK * 2, XSTAGE = XA + XBN * XBK * 2;  // bytes
 constexpr int XGEMM_LDS_BYTES = XNST * XSTAGE;
 static_assert(XGEMM_LDS_BYTES <= 160 * 1024, "one workgroup per compute unit");
@@ -931,9 +936,9 @@ __global__ void __launch_bounds__(XT, 1) gemm256_kernel(GemmArgs g) {
     boff[u] = static_cast<uint32_t>(min(row, nrows - 1) * ld * 2) + bcol * 2;
   }
   // LDS stage: the A fragments [k-step][token block], then the B blocks. This
-  // wave's part of a k-tile is 8 loads (A and B in turn); sa, sb: the k-tile's
-  // byte offsets in A and in a row of B; la, lb: this wave's places in the stage.
-  uint32_t sa = kt0 * 2 * akstep, sb = kt0 * XBK * 2;
+  // wave's part of a k-tile is 8 loads (A and B in turn); la, lb: its places in
+  // the stage.
+  KWalk walk(kt0, nkt - (tail ? 1 : 0), akstep);
   const uint32_t la0 = lbase + wave * 2048, lb0 = lbase + XA + wave * 4096;
   auto target = [&](auto i, uint32_t stage) {
     constexpr int u = decltype(i)::value / 2;
@@ -942,11 +947,11 @@ __global__ void __launch_bounds__(XT, 1) gemm256_kernel(GemmArgs g) {
   };
   auto load = [&](int i) {
     const int u = i / 2;
-    if (i % 2 == 0) dma16(ra, aoff[u % 2], u / 2 ? sa + akstep : sa);
-    else dma16(rb[u], boff[u], sb);
+    if (i % 2 == 0) dma16(ra, aoff[u % 2], u / 2 ? walk.a1 : walk.a0);
+    else dma16(rb[u], boff[u], walk.b);
   };
-  // Past the last k-tile the loads go on with empty ranges (no memory
-  // traffic, the stage is not read any more), so the counts stay the same.
+  // Past the last k-tile the loads go on with empty ranges from offset 0 (no
+  // memory traffic, the stage is not read any more), so the counts stay the same.
   auto no_more = [&]() {
     ra.z = 0;
 #pragma unroll
@@ -1011,14 +1016,12 @@ __global__ void __launch_bounds__(XT, 1) gemm256_kernel(GemmArgs g) {
   // XNST - 3 k-tiles' loads.
   auto landed = [&]() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(8 * (XNST - 3)) : "memory"); };
   const int shift = tail ? 1 : 0;
-  int issued = shift;  // k-tiles of the work order issued
   auto advance = [&]() {
-    sa += 2 * akstep;
-    sb += XBK * 2;
-    if (++issued >= nkt) no_more();
+    walk.next();
+    if (walk.done()) no_more();
   };
   if (tail) stage_tail();
-  if (issued >= nkt) no_more();
+  if (walk.done()) no_more();
   each<XNST - 1>([&](auto Q) {
     constexpr int q = decltype(Q)::value;
     if (q >= shift) {
@@ -1911,6 +1914,20 @@ size_t prefill_workspace_bytes(const vt_shard_spec& s, int32_t max_tokens, int32
 }  // namespace vt
 
 using namespace vt;
+
+// Host replay of gemm256_kernel's loads for tests: the scalar offsets and the
+// emptiness of the ranges of each k-tile a slice of nkt k-tiles from kt0 issues,
+// 4 words (a0, a1, b, empty) each. Returns their number.
+extern "C" int vt_test_prefill_walk(int32_t M, int32_t K, int32_t kt0, int32_t nkt, uint32_t* out, int32_t cap) {
+  const int KT = (K + pf::XBK - 1) / pf::XBK, shift = kt0 + nkt == KT && K % pf::XBK != 0;
+  pf::KWalk walk(kt0, nkt - shift, static_cast<uint32_t>(M) * 32u);
+  int n = 0;
+  for (; n < pf::XNST - 1 - shift + nkt && n < cap; ++n, walk.next()) {
+    const uint32_t w[4] = {walk.a0, walk.a1, walk.b, walk.done()};
+    std::copy(w, w + 4, out + 4 * n);
+  }
+  return n;
+}
 
 extern "C" vt_status vt_layer_prefill_chunk(const vt_shard_spec* spec, const vt_layer_weights* w,
                                             vt_kv_view* kv, const vt_layer_io* io, int32_t n_tok,
