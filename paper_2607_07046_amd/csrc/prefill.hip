@@ -651,18 +651,37 @@ constexpr int XA = XBM * XBK * 2, XSTAGE = XA + XBN * XBK * 2;  // bytes
 constexpr int XGEMM_LDS_BYTES = XNST * XSTAGE;
 static_assert(XGEMM_LDS_BYTES <= 160 * 1024, "one workgroup per compute unit");
 
-// 16 bytes per lane from r[voff + soff] to LDS byte m0 + 16 * lane. m0 is set
-// by dma_to(), with at least one instruction in between.
+// 16 bytes per lane from r[voff + soff] to LDS byte base + OFF + 16 * lane. The
+// target goes through m0: dma16 sets it in the block of the load, with the
+// wait state between; dma_to and dma_from are its halves for a loop that has a
+// product to issue in between. The clobber keeps the compiler's own writes of m0
+// from moving across, and a test of its output shows that it has none
+// between the halves. (The warning is that m0 is not saved: it is reserved,
+// so nothing is kept in it.)
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
+template <int OFF>
+__device__ __forceinline__ void dma16(uint32_t base, u32x4 r, uint32_t voff, uint32_t soff) {
+  asm volatile("s_add_u32 m0, %0, %1\n\ts_nop 0\n\tbuffer_load_dwordx4 %2, %3, %4 offen lds"
+               :
+               : "s"(__builtin_amdgcn_readfirstlane(base)), "n"(OFF), "v"(voff), "s"(r),
+                 "s"(__builtin_amdgcn_readfirstlane(soff))
+               : "m0", "scc", "memory");
+}
 template <int OFF>
 __device__ __forceinline__ void dma_to(uint32_t base) {
-  asm volatile("s_add_u32 m0, %0, %1" : : "s"(__builtin_amdgcn_readfirstlane(base)), "n"(OFF) : "scc", "memory");
+  asm volatile("s_add_u32 m0, %0, %1"
+               :
+               : "s"(__builtin_amdgcn_readfirstlane(base)), "n"(OFF)
+               : "m0", "scc", "memory");
 }
-__device__ __forceinline__ void dma16(u32x4 r, uint32_t voff, uint32_t soff) {
+__device__ __forceinline__ void dma_from(u32x4 r, uint32_t voff, uint32_t soff) {
   asm volatile("buffer_load_dwordx4 %0, %1, %2 offen lds"
                :
                : "v"(voff), "s"(r), "s"(__builtin_amdgcn_readfirstlane(soff))
                : "memory");
 }
+#pragma clang diagnostic pop
 
 // The same descriptor as make_rsrc, as four scalar words.
 __device__ __forceinline__ u32x4 rsrc_words(const void* base, uint32_t bytes) {
@@ -940,15 +959,15 @@ __global__ void __launch_bounds__(XT, 1) gemm256_kernel(GemmArgs g) {
   // the stage.
   KWalk walk(kt0, nkt - (tail ? 1 : 0), akstep);
   const uint32_t la0 = lbase + wave * 2048, lb0 = lbase + XA + wave * 4096;
-  auto target = [&](auto i, uint32_t stage) {
+  auto base = [&](int i, uint32_t stage) { return (i % 2 == 0 ? la0 : lb0) + stage; };
+  auto target = [](auto i) {  // load i's place from there
     constexpr int u = decltype(i)::value / 2;
-    if constexpr (decltype(i)::value % 2 == 0) dma_to<(u / 2 * 8 + u % 2) * 1024>(la0 + stage);
-    else dma_to<u * 1024>(lb0 + stage);
+    return std::integral_constant<int, (decltype(i)::value % 2 == 0 ? u / 2 * 8 + u % 2 : u) * 1024>{};
   };
-  auto load = [&](int i) {
+  auto with = [&](int i, auto&& f) {  // load i's operands
     const int u = i / 2;
-    if (i % 2 == 0) dma16(ra, aoff[u % 2], u / 2 ? walk.a1 : walk.a0);
-    else dma16(rb[u], boff[u], walk.b);
+    if (i % 2 == 0) f(ra, aoff[u % 2], u / 2 ? walk.a1 : walk.a0);
+    else f(rb[u], boff[u], walk.b);
   };
   // Past the last k-tile the loads go on with empty ranges from offset 0 (no
   // memory traffic, the stage is not read any more), so the counts stay the same.
@@ -1005,8 +1024,9 @@ __global__ void __launch_bounds__(XT, 1) gemm256_kernel(GemmArgs g) {
       constexpr int i = decltype(I)::value, a = i / 8, b = i % 8;
       acc[a][b] = mfma16(af[set][a], bf[set][b], acc[a][b]);
       if constexpr (i < 32 && i % 2 == 0) read1(i / 2, stage, 1 - set);
-      if constexpr (i >= 32 && i % 4 == 0) target(std::integral_constant<int, (i - 32) / 4>{}, into);
-      if constexpr (i >= 32 && i % 4 == 2) load((i - 32) / 4);
+      if constexpr (i >= 32 && i % 4 == 0)
+        dma_to<decltype(target(std::integral_constant<int, (i - 32) / 4>{}))::value>(base((i - 32) / 4, into));
+      if constexpr (i >= 32 && i % 4 == 2) with((i - 32) / 4, dma_from);
       __builtin_amdgcn_sched_barrier(0);
     });
   };
@@ -1026,9 +1046,9 @@ __global__ void __launch_bounds__(XT, 1) gemm256_kernel(GemmArgs g) {
     constexpr int q = decltype(Q)::value;
     if (q >= shift) {
       each<8>([&](auto i) {
-        target(i, q * XSTAGE);
-        asm volatile("s_nop 0");
-        load(decltype(i)::value);
+        with(i, [&](u32x4 r, uint32_t voff, uint32_t soff) {
+          dma16<decltype(target(i))::value>(base(i, q * XSTAGE), r, voff, soff);
+        });
       });
       advance();
     }
@@ -1525,12 +1545,8 @@ __global__ void __launch_bounds__(LT, 2) attn_long_kernel(const uint16_t* Q, uin
     const uint32_t base = lbase + stage + kw * 2 * TILE + qg * LPW * 1024;
 #pragma unroll
     for (int u = 0; u < LPW; ++u) {
-      dma_to<0>(base + u * 1024);
-      asm volatile("s_nop 0");
-      dma16(rk, static_cast<uint32_t>(min(p0 + krow[u], last_key)) * (D * 2u) + kcol[u], 0);
-      dma_to<TILE>(base + u * 1024);
-      asm volatile("s_nop 0");
-      dma16(rv, static_cast<uint32_t>(min(p0 + vrow[u], last_key)) * (D * 2u) + vcol[u], 0);
+      dma16<0>(base + u * 1024, rk, static_cast<uint32_t>(min(p0 + krow[u], last_key)) * (D * 2u) + kcol[u], 0);
+      dma16<TILE>(base + u * 1024, rv, static_cast<uint32_t>(min(p0 + vrow[u], last_key)) * (D * 2u) + vcol[u], 0);
     }
   };
 #pragma unroll

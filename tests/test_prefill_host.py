@@ -2,10 +2,14 @@
 loads and launches are computed from is shared with the host or visible in
 the compiler's output."""
 import ctypes
+import os
+import re
+import subprocess
 
 import numpy as np
 import pytest
 
+from paper_2607_07046_amd import build
 from paper_2607_07046_amd import voltron as vt
 
 
@@ -35,3 +39,31 @@ def test_direct_loads_stay_in_their_ranges(lib, M, K, kt0, nkt):
         full += 1
         assert a1 + M * 32 <= a_bytes and b + 64 <= row_bytes
     assert full == nkt - tail and n > full
+
+
+def test_direct_loads_keep_their_target(tmp_path):
+    """A load into LDS takes its target from m0, which the compiler may write
+    too: every inline write of m0 names it as changed, and in the compiler's output
+    each load follows a write of its own, an instruction or more ahead, with
+    no other use of m0 anywhere."""
+    source = os.path.join(build.CSRC, "prefill.hip")
+    with open(source) as f:
+        writes = [b for b in re.findall(r"asm volatile\((.*?)\);", f.read(), re.S) if re.search(r"\bm0,", b)]
+    assert writes and all('"m0"' in b for b in writes)
+    out = tmp_path / "prefill.s"
+    subprocess.run([build.HIPCC, *build.FLAGS, "-I", os.path.join(build.ROOT, "include"), "-I", build.CSRC,
+                    "--cuda-device-only", "-S", source, "-o", str(out)], check=True, capture_output=True)
+    loads, since = 0, None  # instructions since the target was set
+    for line in out.read_text().split("\n"):
+        t = line.split(";")[0].strip()
+        if not t or t.startswith(".") or t.endswith(":"):
+            continue
+        if re.search(r"\bm0\b", t):
+            assert re.match(r"s_add_u32 m0, s\d+, \w+$", t) and since is None, t
+            since = 0
+        elif re.search(r"\blds$", t):
+            assert since is not None and since >= 1, t
+            loads, since = loads + 1, None
+        elif since is not None:
+            since += 1
+    assert loads and since is None
