@@ -1491,9 +1491,10 @@ __global__ void __launch_bounds__(AW * kWave) attn_prefill_kernel(const uint16_t
 // c ^ 2 (r % 8) (r % 4) for V, whose transposing reads take two chunks of four
 // rows. K rows are permuted as in attn_prefill_kernel. Keys past the last one
 // the workgroup attends read that one instead (and are masked).
-// The sums of probabilities stay per lane until the end and are of the values
-// as rounded for the second product, so that a rounding moves numerator and
-// denominator together; exp(s - m) is one fma and one exp2.
+// The sums of probabilities stay per lane until the end. Scores and running
+// maximum are subtracted before anything is rounded, in the weights, in the
+// rescale and in the merge: exp2(s log2e - m log2e) in one fma was as fast, but its
+// weights belong to a rounded reference that the rescale has to use too.
 // ---------------------------------------------------------------------------
 constexpr int LQ = 128, LQST = 4, KW = 2, LT = 256 * KW;
 
@@ -1560,7 +1561,6 @@ __global__ void __launch_bounds__(LT, 2) attn_long_kernel(const uint16_t* Q, uin
 #pragma unroll
   for (int mt = 0; mt < D / 32; ++mt) o[mt] = f32x16{};
   float mrun = -INFINITY, lrun = 0.f;
-  constexpr float kLog2e = 1.44269504088896340736f;
 
   const int kr = lane % 32;
   const int kaddr = kw * 2 * TILE + kr * D * 2, kx = kr % CPR;
@@ -1617,10 +1617,10 @@ __global__ void __launch_bounds__(LT, 2) attn_long_kernel(const uint16_t* Q, uin
     for (int i = 1; i < 16; ++i) bm = fmaxf(bm, s[i]);
     bm = fmaxf(bm, __shfl_xor(bm, 32, kWave));
     const float mnew = fmaxf(mrun, bm);
-    // a query that has seen no key yet keeps a zero reference: exp2(-inf) = 0
-    const float ml = mnew == -INFINITY ? 0.f : mnew * kLog2e;
+    // a query that has seen no key yet has zero as its reference: exp(-inf) = 0
+    const float ref = mnew == -INFINITY ? 0.f : mnew;
     if (__builtin_amdgcn_ballot_w64(mnew != mrun) != 0) {
-      const float alpha = __builtin_amdgcn_exp2f(fmaf(mrun, kLog2e, -ml));
+      const float alpha = __expf(mrun - ref);
       lrun *= alpha;
 #pragma unroll
       for (int mt = 0; mt < D / 32; ++mt)
@@ -1634,8 +1634,9 @@ __global__ void __launch_bounds__(LT, 2) attn_long_kernel(const uint16_t* Q, uin
       uint16_t h[8];
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
-        h[e] = f2h(__builtin_amdgcn_exp2f(fmaf(s[8 * s2 + e], kLog2e, -ml)));
-        lrun += h2f(h[e]);
+        const float p = __expf(s[8 * s2 + e] - ref);
+        lrun += p;
+        h[e] = f2h(p);
       }
       pf[s2] = pack8(h);
     }
@@ -1661,9 +1662,8 @@ __global__ void __launch_bounds__(LT, 2) attn_long_kernel(const uint16_t* Q, uin
   __syncthreads();
   if (kw == 1) return;
   const float m1 = part[(D / 2) * kWave], l1 = part[(D / 2 + 1) * kWave];
-  const float ms = fmaxf(mrun, m1), ml = ms == -INFINITY ? 0.f : ms * kLog2e;
-  const float a0 = __builtin_amdgcn_exp2f(fmaf(mrun, kLog2e, -ml));
-  const float a1 = __builtin_amdgcn_exp2f(fmaf(m1, kLog2e, -ml));
+  const float ms = fmaxf(mrun, m1), ref = ms == -INFINITY ? 0.f : ms;
+  const float a0 = __expf(mrun - ref), a1 = __expf(m1 - ref);
   lrun = lrun * a0 + l1 * a1;
 #pragma unroll
   for (int mt = 0; mt < D / 32; ++mt)

@@ -152,3 +152,43 @@ ATTN_EDGES = [
 @pytest.mark.parametrize("shape", ATTN_EDGES, ids=[f"T{s[0]}-q{s[2]}-d{s[4]}-w{s[7]}" for s in ATTN_EDGES])
 def test_long_attention_edges(shape):
     run_layer(*shape, seed=1)
+
+
+def test_long_attention_large_scores():
+    """Scores of 2^17 and an eighth more from key block to key block, exact in fp32:
+    every block moves the running maximum. The values tell the last eight blocks
+    from the others, so a weight that changes with the rescales shows."""
+    T, H, heads, d, ctx = 1793, 64, 16, 64, 2048
+    g = torch.Generator(device="cuda").manual_seed(5)
+    dims = vt.vt_layer_dims(hidden=H, n_heads=heads, n_kv_heads=heads, head_dim=d, ffn=64, rms_eps=1e-6,
+                            rope_base=1e30, window=0)
+    spec = vt.vt_shard_spec_create(dims, [1.0], [1.0], 0)
+    dims, info = vt.vt_shard_spec_query(spec)
+    x = torch.sign(_normal(g, (T, H), 1.0))
+    x[x == 0] = 1.0
+    x[:, 0] = 1.0  # the norm of +-1 rows is 1: u = x to the bit
+    one = lambda n: torch.ones(n, dtype=torch.float16, device="cuda")
+    w = {"g_attn": one(H), "g_ffn": one(H)}
+    for n, rows in (("wq", heads * d), ("wk", heads * d), ("wv", heads * d)):
+        w[n] = torch.zeros((rows, H), dtype=torch.float16, device="cuda")
+    w["wq"][62::d, 0], w["wq"][63::d, 0] = 2048.0, 1.0  # the last pair does not rotate at this base
+    w["wo"] = _normal(g, (H, heads * d), 1.0 / math.sqrt(heads * d))
+    w["wg"], w["wu"], w["wd"] = (_normal(g, (64, 64), 0.1) for _ in range(3))
+    kc = torch.zeros((heads, ctx + T, d), dtype=torch.float16, device="cuda")
+    vc = torch.zeros_like(kc)
+    block = torch.arange(ctx, device="cuda") // 32
+    kc[:, :ctx, 62], kc[:, :ctx, 63] = 512.0, block.half()
+    sign = torch.where(block < 56, 1.0, -1.0)
+    vc[:, :ctx] = (sign[None, :, None] * (1.0 + 0.25 * torch.rand((heads, 1, d), generator=g, device="cuda"))).half()
+    ws = torch.zeros(vt.vt_workspace_size(spec, T, ctx + T), dtype=torch.uint8, device="cuda")
+    out = {n: torch.empty((T, H), dtype=torch.float16, device="cuda") for n in ("p", "h")}
+    io = vt.vt_layer_io(x=x.data_ptr(), attn_partial=out["p"].data_ptr(), h=out["h"].data_ptr())
+    view = vt.vt_kv_view(k=kc.data_ptr(), v=vc.data_ptr(), capacity=ctx + T, n_kv_heads=heads, head_dim=d, len=ctx)
+    vt.vt_layer_prefill_chunk(spec, pack.struct_of(w, dims, info, 64), view, io, T, ctx, vt.VT_ATTN, ws.data_ptr(),
+                              ws.numel(), torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    # the chunk's own keys are zero: 1.3e5 below the others, weight 0
+    assert not kc[:, ctx:].any()
+    p = torch.softmax((2048.0 * 512.0 + block.double()) / 8.0, 0)
+    o = (p[None, :, None] * vc[:, :ctx].double()).sum(1).reshape(1, -1)
+    _close(out["p"], (o @ w["wo"].double().T).expand(T, H), "p_attn")
