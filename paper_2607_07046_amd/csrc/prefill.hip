@@ -1647,6 +1647,19 @@ __global__ void __launch_bounds__(LT, 2) attn_long_kernel(const uint16_t* Q, uin
       }
       pf[s2] = pack8(h);
     }
+    if (p0 + KB - 1 > wave_last) {
+      // values after this wave's last query stay out even if they are infinite:
+      // vf[mt][s2][q] holds keys 16 s2 + 8 (l/32) + 4 q ..
+#pragma unroll
+      for (int s2 = 0; s2 < 2; ++s2)
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            if (p0 + 16 * s2 + 8 * (lane / 32) + 4 * q + e > wave_last)
+#pragma unroll
+              for (int mt = 0; mt < D / 32; ++mt) vf[mt][s2][q][e] = 0;
+    }
 #pragma unroll
     for (int mt = 0; mt < D / 32; ++mt)
 #pragma unroll

@@ -215,3 +215,42 @@ def test_long_attention_large_scores():
     p = torch.softmax((2048.0 * 512.0 + block.double()) / 8.0, 0)
     o = (p[None, :, None] * vc[:, :ctx].double()).sum(1).reshape(1, -1)
     _close(out["p"], (o @ w["wo"].double().T).expand(T, H), "p_attn")
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_long_attention_infinite_value_after_the_queries(d):
+    """A token whose value overflows to infinity leaves the queries of the 32-token
+    groups before its own as they are, though it shares their last key block."""
+    T, H, heads, F, ctx, bad = 1793, 512, 16, 64, 5, 32 * 9
+    g = torch.Generator(device="cuda").manual_seed(7)
+    dims = vt.vt_layer_dims(hidden=H, n_heads=heads, n_kv_heads=heads, head_dim=d, ffn=F, rms_eps=EPS,
+                            rope_base=BASE, window=0)
+    spec = vt.vt_shard_spec_create(dims, [1.0], [1.0], 0)
+    dims, info = vt.vt_shard_spec_query(spec)
+    s = 1.0 / math.sqrt(H)
+    w = {n: _normal(g, shape, s) for n, shape in
+         (("wq", (heads * d, H)), ("wk", (heads * d, H)), ("wv", (heads * d, H)), ("wo", (H, heads * d)),
+          ("wg", (F, H)), ("wu", (F, H)), ("wd", (H, F)))}
+    w["g_attn"], w["g_ffn"] = _normal(g, (H,), 0.1, 1.0), _normal(g, (H,), 0.1, 1.0)
+    w["wv"][:, 0] = 3e4
+    x = _normal(g, (T, H), 1.0)
+    x[:, 0] = 0.0
+    outs = []
+    for big in (False, True):
+        if big:
+            x[bad] = 0.0
+            x[bad, 0] = 1.0  # normalised to sqrt(H) = 22.6: a value of 6.8e5
+        kc = torch.zeros((heads, ctx + T, d), dtype=torch.float16, device="cuda")
+        vc = torch.zeros_like(kc)
+        kc[:, :ctx], vc[:, :ctx] = 0.5, 1.0
+        ws = torch.zeros(vt.vt_workspace_size(spec, T, ctx + T), dtype=torch.uint8, device="cuda")
+        out = {n: torch.empty((T, H), dtype=torch.float16, device="cuda") for n in ("p", "h")}
+        io = vt.vt_layer_io(x=x.data_ptr(), attn_partial=out["p"].data_ptr(), h=out["h"].data_ptr())
+        view = vt.vt_kv_view(k=kc.data_ptr(), v=vc.data_ptr(), capacity=ctx + T, n_kv_heads=heads, head_dim=d, len=ctx)
+        vt.vt_layer_prefill_chunk(spec, pack.struct_of(w, dims, info, F), view, io, T, ctx, vt.VT_ATTN, ws.data_ptr(),
+                                  ws.numel(), torch.cuda.current_stream().cuda_stream)
+        torch.cuda.synchronize()
+        assert bool(torch.isinf(vc[:, ctx + bad]).all()) == big
+        outs.append(out["p"])
+    assert torch.isfinite(outs[0]).all()
+    assert torch.equal(outs[0][:bad], outs[1][:bad])
