@@ -1711,17 +1711,14 @@ __global__ void __launch_bounds__(LT, 2) attn_long_kernel(const uint16_t* Q, uin
 // ---------------------------------------------------------------------------
 namespace {
 
-// Tile and split-K choice of a GEMM: the kernel (128 or 256 tile edge) and the
-// slice count S (whole k-tiles each, at most MAX_SPLITS, the in-kernel
-// reduction's width) with the smallest modelled time.
-// 128: the tiles x S workgroups run in rounds of GEMM_SLOTS (two per compute
-// unit); a round in which compute units hold two workgroups advances each by
-// one k-tile per kTwoPerCu microseconds, a last round of at most one per
-// compute unit per kOnePerCu; each of the (S - 1) x tiles fp32 partial tiles
+// Split-K choice of a GEMM on 128 x 128 tiles: the slice count S (whole k-tiles
+// each, at most MAX_SPLITS, the in-kernel reduction's width) with the smallest
+// modelled time. The tiles x S workgroups run in rounds of GEMM_SLOTS (two per
+// compute unit); a round in which compute units hold two workgroups advances
+// each by one k-tile per kTwoPerCu microseconds, a last round of at most one
+// per compute unit per kOnePerCu; each of the (S - 1) x tiles fp32 partial tiles
 // costs kPartial (64 KiB stored and read back at about 7 TB/s). The
-// constants are MI355X measurements of this kernel on the 7B shapes (the
-// per-k-tile rates from the 4096-token chunk's GEMMs, which the model then
-// reproduced within 5%, the partial-tile cost from the chip's copy rate). It
+// constants are MI355X measurements of this kernel on the 7B shapes. It
 // takes fewer slices than a rule of about two rounds of workgroups: at 256
 // tokens 2 instead of 4 for QKV (the same time, 2.5 times less partial-tile
 // traffic), and at 512 / 1024 / 2048 tokens per chunk 0.222 / 0.340 /
@@ -1732,41 +1729,91 @@ struct Split {
 };
 
 constexpr double kTwoPerCu = 1.33, kOnePerCu = 0.75, kPartial = 0.0187;
-// 256: rounds of one workgroup per compute unit, kBig per k-tile and kBigFixed
-// (the first loads, the epilogue) each, and kBigSplit besides the partial
-// tiles if split. Measured on the 7B shapes at 4096 tokens: QKV 204 us (228
-// with the 128 tile), O 87 (98), gate/up 338 (425), down 162 (211); at 1024
-// gate/up 104 (130) but O 66 (39) and down 78 (71); at 256 every GEMM is
-// slower (QKV 54 against 34): few large tiles leave compute units idle.
-constexpr int kBigSlots = 256;
-constexpr double kBig = 1.25, kBigFixed = 27.0, kBigSplit = 15.0, kSmallFixed = 3.0;
 
-Split choose_split(int M, int N, int K) {
+Split tiles_of(int bm, int M, int N, int K, int want) {
+  const int KT = std::max(1, (K + pf::GBK - 1) / pf::GBK);
+  const int kps = (KT + want - 1) / want;
+  return Split{bm, (M + bm - 1) / bm, (N + bm - 1) / bm, (KT + kps - 1) / kps, kps};
+}
+
+Split small_split(int M, int N, int K) {
   const int KT = std::max(1, (K + pf::GBK - 1) / pf::GBK);
   Split s{};
   double best = 0.0;
-  for (int bm : {pf::GBM, pf::XBM}) {
-    const int m_tiles = (M + bm - 1) / bm, n_tiles = (N + bm - 1) / bm;
-    const int64_t tiles = std::max(1, m_tiles * n_tiles);
-    for (int want = 1; want <= std::min(KT, pf::MAX_SPLITS); ++want) {
-      const int kps = (KT + want - 1) / want;
-      const int splits = (KT + kps - 1) / kps;
-      const int64_t groups = tiles * splits;
-      double t;
-      if (bm == pf::GBM) {
-        const int64_t full = groups / pf::GEMM_SLOTS, rest = groups % pf::GEMM_SLOTS;
-        t = static_cast<double>(full) * kps * kTwoPerCu + kSmallFixed;
-        if (rest > pf::GEMM_SLOTS / 2) t += kps * kTwoPerCu;
-        else if (rest > 0) t += kps * kOnePerCu;
-        t += static_cast<double>(splits - 1) * static_cast<double>(tiles) * kPartial;
-      } else {
-        t = static_cast<double>((groups + kBigSlots - 1) / kBigSlots) * (kps * kBig + kBigFixed);
-        if (splits > 1) t += kBigSplit + static_cast<double>(splits - 1) * static_cast<double>(tiles) * 4 * kPartial;
-      }
-      if (best == 0.0 || t < best) {
-        best = t;
-        s = Split{bm, m_tiles, n_tiles, splits, kps};
-      }
+  for (int want = 1; want <= std::min(KT, pf::MAX_SPLITS); ++want) {
+    const Split c = tiles_of(pf::GBM, M, N, K, want);
+    const int64_t tiles = std::max(1, c.m_tiles * c.n_tiles), groups = tiles * c.splits;
+    const int64_t full = groups / pf::GEMM_SLOTS, rest = groups % pf::GEMM_SLOTS;
+    double t = static_cast<double>(full) * c.kps * kTwoPerCu;
+    if (rest > pf::GEMM_SLOTS / 2) t += c.kps * kTwoPerCu;
+    else if (rest > 0) t += c.kps * kOnePerCu;
+    t += static_cast<double>(c.splits - 1) * static_cast<double>(tiles) * kPartial;
+    if (want == 1 || t < best) {
+      best = t;
+      s = c;
+    }
+  }
+  return s;
+}
+
+// Which tile: the 128 one as split above or the 256 one with its best slice
+// count, by the modelled times of both (microseconds). Fitted to the traced
+// times of both kernels in 1-4 slices on 114 drawn and named layers (hidden 512 to
+// 8192, 131 to 4096 tokens; median error 4%, nine in ten within 12%).
+// * A row of B whose length is no multiple of 64 bytes (K is no multiple of 32 after
+//   rounding up to 8) straddles the memory's lines: more per k-tile for both, a
+//   fifth more for the large tile (hidden 6000, 2035 tokens, gate/up: 353 us against
+//   290 for the small tile).
+// * The large tile runs one workgroup per compute unit and an XCD's share in its
+//   own 32: a round begins when the fullest XCD has more. 7 x 33 tiles are two
+//   rounds (5 x 7 on one XCD): 208 us against 176 for the small tile.
+// * Both read B once (per byte), and O and down move 10 bytes per output in
+//   the epilogue, of which the large tile hides less.
+// * A modelled small-tile time below kSmallEnough is taken without a look at the other: no
+//   shape measured below it was faster on the large tile, whose first loads and
+//   epilogue take 20-35 us.
+// Over the shapes measured (one time per GEMM): 63.6 ms with this rule, 63.9 with
+// whole rounds of 256 workgroups as the large tile's only cost, 70.3 on the small
+// tile alone, 63.3 with the better of both each time.
+constexpr double kSmallEnough = 60.0;
+
+double misaligned(int K) { return (K + 7) / 8 * 8 % 32 != 0 ? 1.0 : 0.0; }
+// Outputs and weights in millions; rows rounded up, so that the choice depends on M only
+// through its number of 128-row tiles.
+double outputs(int M, int N) { return (M + pf::GBM - 1) / pf::GBM * static_cast<double>(pf::GBM) * N * 1e-6; }
+double weights(int N, int K) { return static_cast<double>(N) * K * 1e-6; }
+
+double small_us(const Split& c, int M, int N, int K, bool residual) {
+  const double two = 1.18 + 0.14 * misaligned(K), one = 0.60 + 0.07 * misaligned(K);
+  const int64_t tiles = std::max(1, c.m_tiles * c.n_tiles), groups = tiles * c.splits, half = pf::GEMM_SLOTS / 2;
+  const int64_t rest = groups % pf::GEMM_SLOTS;
+  double t = static_cast<double>(groups / pf::GEMM_SLOTS) * c.kps * two + 16.0;
+  if (rest > half) t += c.kps * (one + (two - one) * static_cast<double>(rest - half) / half);
+  else if (rest > 0) t += c.kps * one;
+  return t + 0.016 * static_cast<double>(c.splits - 1) * static_cast<double>(tiles) +
+         (residual ? 1.0 * outputs(M, N) : 0.0) + 0.031 * weights(N, K);
+}
+
+double big_us(const Split& c, int M, int N, int K, bool residual) {
+  const int xcd = (c.n_tiles * c.splits + 7) / 8 * c.m_tiles;  // workgroups of the fullest XCD
+  double t = static_cast<double>((xcd + 31) / 32) * (c.kps * (1.27 + 0.27 * misaligned(K)) + 3.0) +
+             (residual ? 3.1 : 1.6) * outputs(M, N) + 0.16 * weights(N, K);
+  if (c.splits > 1) t += 15.7 + 0.079 * (c.splits - 1) * c.m_tiles * c.n_tiles;
+  return t;
+}
+
+// residual: O or down, whose epilogue adds the residual stream
+Split choose_split(int M, int N, int K, bool residual) {
+  Split s = small_split(M, N, K);
+  double best = small_us(s, M, N, K, residual);
+  if (best < kSmallEnough) return s;
+  const int KT = std::max(1, (K + pf::GBK - 1) / pf::GBK);
+  for (int want = 1; want <= std::min(KT, pf::MAX_SPLITS); ++want) {
+    const Split c = tiles_of(pf::XBM, M, N, K, want);
+    const double t = big_us(c, M, N, K, residual);
+    if (t < best) {
+      best = t;
+      s = c;
     }
   }
   return s;
@@ -1812,7 +1859,7 @@ PrefillWs prefill_layout(const vt_shard_spec& s, int32_t T) {
   int64_t part = 0;  // one region serves the four GEMMs' split-K tiles in turn
   w.ncnt = 0;
   for (int i = 0; i < 4; ++i) {
-    const Split sp = choose_split(gm.M, gm.N[i], gm.K[i]);
+    const Split sp = choose_split(gm.M, gm.N[i], gm.K[i], i == 1 || i == 3);
     const int64_t tiles = static_cast<int64_t>(sp.m_tiles) * sp.n_tiles;
     if (sp.splits > 1) part = std::max<int64_t>(part, sp.splits * tiles * sp.bm * sp.bm * 4);
     w.cnt_off[i] = w.ncnt;
@@ -1863,7 +1910,7 @@ constexpr GemmKernel kBigKernels[2][4] = {
 // Launches the split-K GEMM with its epilogue; P holds the split-K tiles and
 // cnt the per-tile arrival counters (zero at launch).
 vt_status launch_gemm(pf::GemmArgs a, float* P, unsigned* cnt, unsigned* err, hipStream_t s) {
-  const Split sp = choose_split(a.M, a.N, a.K);
+  const Split sp = choose_split(a.M, a.N, a.K, a.epi == pf::EPI_O || a.epi == pf::EPI_DOWN);
   a.m_tiles = sp.m_tiles;
   a.n_tiles = sp.n_tiles;
   a.splits = sp.splits;
@@ -1963,6 +2010,13 @@ extern "C" int vt_test_prefill_walk(int32_t M, int32_t K, int32_t kt0, int32_t n
     std::copy(w, w + 4, out + 4 * n);
   }
   return n;
+}
+
+// The tile edge a prefill GEMM takes, and its slices, for tests.
+extern "C" int vt_test_prefill_tile(int32_t M, int32_t N, int32_t K, int32_t residual, int32_t* splits) {
+  const Split sp = choose_split(M, N, K, residual != 0);
+  *splits = sp.splits;
+  return sp.bm;
 }
 
 extern "C" vt_status vt_layer_prefill_chunk(const vt_shard_spec* spec, const vt_layer_weights* w,

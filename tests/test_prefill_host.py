@@ -67,3 +67,30 @@ def test_direct_loads_keep_their_target(tmp_path):
         elif since is not None:
             since += 1
     assert loads and since is None
+
+
+# tokens, N, K, an epilogue with the residual stream (O, down), traced us on the
+# small and the large tile
+TILE_TIMES = [(3000, 5120, 2048, 1, 101.8, 138.3), (617, 31360, 4616, 0, 245.4, 280.1), (145, 30848, 5328, 0, 115.3, 123.1),
+              (888, 6912, 5120, 0, 101.5, 90.1), (160, 57344, 8192, 0, 368.4, 267.8), (4096, 6144, 4096, 0, 228.0, 204.0),
+              (777, 21248, 8192, 0, 366.0, 347.0), (256, 11008, 4096, 0, 48.3, 64.0), (453, 7920, 24295, 1, 284.7, 235.6)]
+
+
+@pytest.mark.parametrize("M,N,K,residual,small,large", TILE_TIMES)
+def test_tile_choice_follows_the_measured_times(lib, M, N, K, residual, small, large):
+    """Products whose two times differ by 5% or more take the faster tile."""
+    splits = ctypes.c_int()
+    tile = lib.vt_test_prefill_tile(M, N, K, residual, ctypes.byref(splits))
+    assert 1 <= splits.value <= 4
+    assert tile == (128 if small < large else 256)
+
+
+def test_tile_choice_depends_on_whole_small_tiles(lib):
+    """The workspace is laid out once per count of 128-row tiles: within one, the
+    choice must not change with the number of tokens."""
+    splits = ctypes.c_int()
+    for N, K, residual in ((22016, 4096, 0), (5120, 5530, 1), (8192, 10609, 1), (6912, 5120, 0), (31360, 4616, 0)):
+        for tiles in range(1, 33):
+            seen = {(lib.vt_test_prefill_tile(M, N, K, residual, ctypes.byref(splits)), splits.value)
+                    for M in (128 * tiles - 127, 128 * tiles - 60, 128 * tiles)}
+            assert len(seen) == 1, (N, K, tiles, seen)
