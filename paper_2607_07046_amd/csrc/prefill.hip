@@ -1938,13 +1938,45 @@ vt_status launch_gemm(pf::GemmArgs a, float* P, unsigned* cnt, unsigned* err, hi
   return e == hipSuccess ? VT_OK : fail(VT_ERR_HIP, "gemm launch: %s", hipGetErrorString(e));
 }
 
-// Workgroups of 128 queries from which attn_long_kernel is the faster one.
-// Measured at 16 heads of 128 dimensions, positions 768..: 64 workgroups (512
-// tokens) 34.5 us against 20.6 for attn_prefill_kernel, 128 (1024) 47 against 45,
-// 256 (2048) 72 against 98, 512 (4096) 155 against 254; at 24 heads,
-// positions 2049..: 168 (777) 80 against 82, no gain worth another summation.
-// Below, whole compute units idle.
-constexpr int kLongGroups = 224;
+// Which attention kernel: the modelled times of both (microseconds), from the key
+// blocks of 32 that their workgroups walk. attn_long_kernel's time is that of its
+// fullest compute unit: the longest workgroup (no query block of a causal chunk
+// is longer than its last), or, from 257 workgroups on, one of the first round and
+// the one that follows it, or the average. attn_prefill_kernel's workgroups of
+// 32 queries are many and short: the average. Fitted to both kernels' times on 159
+// chunks (1 to 128 heads, contexts of 0 to 8140, windows of 128 and 1024, 128
+// to 4096 tokens; median error 5%). A count of workgroups alone (224) took the shared blocks
+// at head size 64, 8 heads and 3585 tokens from position 0, whose last query
+// block walks 113 key blocks by itself: 73 us against 53. All chunks measured:
+// 12.7 ms with this rule, 12.8 with the count, 14.9 without the shared blocks.
+bool long_attention(int T, int nq, int d, int pos0, int window) {
+  struct Fit {
+    double start, block, pair, even;         // attn_long_kernel
+    double start32, block32, workgroup32;    // attn_prefill_kernel
+  };
+  constexpr Fit f128 = {11.0, 0.77, 1.0, 1.1, 8.4, 0.315, 2.64}, f64 = {6.7, 0.59, 0.69, 0.75, 5.1, 0.174, 1.76};
+  const Fit& f = d == 128 ? f128 : f64;
+  const double cus = 256.0;
+  auto blocks = [&](int t0, int q) {  // key blocks of the q queries from t0
+    const int last = pos0 + std::min(t0 + q, T) - 1;
+    const int first = window > 0 ? std::max(0, pos0 + t0 - window + 1) : 0;
+    return last / pf::KB - first / pf::KB + 1;
+  };
+  const int nqb = (T + pf::LQ - 1) / pf::LQ, n32 = (T + pf::QB - 1) / pf::QB;
+  double most = 0.0, all = 0.0, all32 = 0.0;
+  for (int i = 0; i < nqb; ++i) {
+    const double b = blocks(i * pf::LQ, pf::LQ);
+    most = std::max(most, b);
+    all += b;
+  }
+  for (int i = 0; i < n32; ++i) all32 += blocks(i * pf::QB, pf::QB);
+  double fullest = std::max(most, f.even * all * nq / cus);
+  if (static_cast<int64_t>(nq) * nqb > 256)  // workgroups 255 and 256, the last query blocks first
+    fullest = std::max(fullest, f.pair * (blocks((nqb - 1 - 255 / nq) * pf::LQ, pf::LQ) +
+                                          blocks((nqb - 1 - 256 / nq) * pf::LQ, pf::LQ)));
+  return f.start + f.block * fullest <
+         f.start32 + (f.block32 * all32 + f.workgroup32 * n32) * nq / cus;
+}
 
 template <int D>
 vt_status launch_attention_d(const uint16_t* Q, uint16_t* O, const vt_kv_view& kv, int T, int nq, int G, int pos0,
@@ -1952,7 +1984,7 @@ vt_status launch_attention_d(const uint16_t* Q, uint16_t* O, const vt_kv_view& k
   const uint16_t* kc = static_cast<const uint16_t*>(kv.k);
   const uint16_t* vc = static_cast<const uint16_t*>(kv.v);
   const int heads8 = (nq + 7) / 8 * 8, qblocks = (T + pf::LQ - 1) / pf::LQ;
-  if (static_cast<int64_t>(nq) * qblocks >= kLongGroups) {
+  if (long_attention(T, nq, D, pos0, window)) {
     constexpr int lds = pf::LQST * 2 * pf::KW * pf::KB * D * 2;
     static std::mutex mu;
     static std::vector<char> raised;
@@ -2010,6 +2042,11 @@ extern "C" int vt_test_prefill_walk(int32_t M, int32_t K, int32_t kt0, int32_t n
     std::copy(w, w + 4, out + 4 * n);
   }
   return n;
+}
+
+// Whether a chunk takes attn_long_kernel, for tests.
+extern "C" int vt_test_long_attention(int32_t T, int32_t nq, int32_t d, int32_t pos0, int32_t window) {
+  return long_attention(T, nq, d, pos0, window);
 }
 
 // The tile edge a prefill GEMM takes, and its slices, for tests.

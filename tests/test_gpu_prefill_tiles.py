@@ -18,6 +18,11 @@ BOTH = vt.VT_ATTN | vt.VT_FFN
 EPS, BASE = 1e-5, 10000.0
 
 
+def shared_blocks(T, heads, d, ctx, window=0):
+    """Whether the chunk's attention shares key blocks between 128 queries."""
+    return bool(vt.load_library().vt_test_long_attention(T, heads, d, ctx, window))
+
+
 def _normal(g, shape, sigma, mean=0.0):
     return torch.empty(shape, dtype=torch.float16, device="cuda").normal_(mean, sigma, generator=g)
 
@@ -155,11 +160,16 @@ ATTN_EDGES = [
     (1665, 512, 18, 18, 128, 64, 500, 128),
     (1542, 512, 20, 20, 64, 64, 7, 1),
     (1792, 512, 16, 16, 128, 64, 40, 0),
+    (3585, 512, 16, 16, 64, 64, 0, 0),
+    (1792, 512, 24, 24, 128, 64, 40, 0),
 ]
+SEPARATE = [ATTN_EDGES[0], ATTN_EDGES[6]]  # the 32-query kernel's, the others the shared blocks'
 
 
 @pytest.mark.parametrize("shape", ATTN_EDGES, ids=[f"T{s[0]}-q{s[2]}-d{s[4]}-w{s[7]}" for s in ATTN_EDGES])
 def test_long_attention_edges(shape):
+    T, _, heads, _, d, _, ctx, window = shape
+    assert shared_blocks(T, heads, d, ctx, window) == (shape not in SEPARATE)
     run_layer(*shape, seed=1)
 
 
@@ -170,6 +180,9 @@ def test_long_attention_error(shape, seed):
     one, which the same tokens take in four chunks (0.4% of the error was lost with one
     exact weight per group of waves; 1e-3 is for the GEMMs' other order of sums)."""
     err = []
+    _, heads, _, d, _, ctx = shape
+    assert shared_blocks(1792, heads, d, ctx)
+    assert not any(shared_blocks(448, heads, d, ctx + t) for t in range(0, 1792, 448))
     for chunks in ([1792], [448] * 4):
         out, ref = run_chunks(chunks, *shape, seed=seed, scale=1.28)
         err.append(float((out["p_attn"][:1792].double() - ref["p_attn"]).norm() / ref["p_attn"].norm()))
@@ -181,7 +194,8 @@ def test_long_attention_large_scores():
     """Scores of 2^17 and an eighth more from key block to key block, exact in fp32:
     every block moves the running maximum. The values tell the last eight blocks
     from the others, so a weight that changes with the rescales shows."""
-    T, H, heads, d, ctx = 1793, 64, 16, 64, 2048
+    T, H, heads, d, ctx = 1793, 64, 32, 64, 2048
+    assert shared_blocks(T, heads, d, ctx)
     g = torch.Generator(device="cuda").manual_seed(5)
     dims = vt.vt_layer_dims(hidden=H, n_heads=heads, n_kv_heads=heads, head_dim=d, ffn=64, rms_eps=1e-6,
                             rope_base=1e30, window=0)
@@ -221,7 +235,8 @@ def test_long_attention_large_scores():
 def test_long_attention_infinite_value_after_the_queries(d):
     """A token whose value overflows to infinity leaves the queries of the 32-token
     groups before its own as they are, though it shares their last key block."""
-    T, H, heads, F, ctx, bad = 1793, 512, 16, 64, 5, 32 * 9
+    T, H, heads, F, ctx, bad = 1793, 512, 32, 64, 5, 32 * 9
+    assert shared_blocks(T, heads, d, ctx)
     g = torch.Generator(device="cuda").manual_seed(7)
     dims = vt.vt_layer_dims(hidden=H, n_heads=heads, n_kv_heads=heads, head_dim=d, ffn=F, rms_eps=EPS,
                             rope_base=BASE, window=0)

@@ -94,3 +94,29 @@ def test_tile_choice_depends_on_whole_small_tiles(lib):
             seen = {(lib.vt_test_prefill_tile(M, N, K, residual, ctypes.byref(splits)), splits.value)
                     for M in (128 * tiles - 127, 128 * tiles - 60, 128 * tiles)}
             assert len(seen) == 1, (N, K, tiles, seen)
+
+
+# tokens, heads, head size, first position, window; traced us with 32 queries per
+# workgroup and with shared key blocks
+ATTENTION_TIMES = [(3585, 8, 64, 0, 0, 53.5, 72.7), (1793, 16, 64, 0, 0, 31.9, 38.5), (2300, 16, 64, 0, 0, 44.7, 51.4),
+                   (130, 128, 64, 1000, 0, 24.2, 26.7), (130, 128, 64, 6000, 0, 101.1, 121.6), (3585, 8, 128, 0, 0, 88.1, 97.9),
+                   (1147, 11, 128, 285, 0, 38.8, 46.2), (180, 32, 128, 7253, 0, 81.8, 187.7), (1131, 7, 64, 248, 0, 15.2, 31.4),
+                   (3876, 8, 64, 2113, 1024, 31.0, 27.1), (450, 128, 64, 6000, 0, 255.6, 171.0), (1055, 64, 64, 16, 0, 56.4, 29.4),
+                   (897, 32, 128, 0, 0, 37.9, 30.8), (2035, 18, 128, 3910, 0, 298.4, 218.0),
+                   (2300, 16, 128, 6000, 0, 331.6, 291.6), (1793, 16, 128, 3000, 1024, 50.0, 38.6)]
+
+
+@pytest.mark.parametrize("T,heads,d,pos0,window,separate,shared", ATTENTION_TIMES)
+def test_attention_choice_follows_the_measured_times(lib, T, heads, d, pos0, window, separate, shared):
+    """Chunks whose two times differ by 10% or more take the faster kernel."""
+    assert lib.vt_test_long_attention(T, heads, d, pos0, window) == (shared < separate)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_attention_choice_over_its_range(lib, d):
+    """Any chunk the entry point takes has a choice, up to one head and 65536
+    tokens, a window longer than the context, and the largest positions."""
+    for T in (1, 127, 128, 129, 4097, 65536):
+        for heads in (1, 7, 255, 256, 257, 1024):
+            for pos0, window in ((0, 0), (0, 1), (5, 100000), (1000000, 0), (1000000, 4096), (2 ** 31 - 1 - T, 0)):
+                assert lib.vt_test_long_attention(T, heads, d, pos0, window) in (0, 1)
