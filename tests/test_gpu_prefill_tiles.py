@@ -4,6 +4,7 @@ and column counts that end inside a k-tile and inside an output tile, one and
 several split-K slices. The reference is the layer in float64 (plain torch on
 the same device); bars as in the oracle's prefill tests.
 """
+import ctypes
 import math
 
 import pytest
@@ -21,6 +22,14 @@ EPS, BASE = 1e-5, 10000.0
 def shared_blocks(T, heads, d, ctx, window=0):
     """Whether the chunk's attention shares key blocks between 128 queries."""
     return bool(vt.load_library().vt_test_long_attention(T, heads, d, ctx, window))
+
+
+def gemm_plan(T, hidden, heads, kv, d, F):
+    """Tile edge and slices of the QKV, O, gate/up and down GEMMs."""
+    n = ctypes.c_int()
+    tile = lambda N, K, residual: (vt.load_library().vt_test_prefill_tile(T, N, K, residual, ctypes.byref(n)), n.value)
+    return [tile((heads + 2 * kv) * d, hidden, 0), tile(hidden, heads * d, 1), tile((F + 63) // 64 * 128, hidden, 0),
+            tile(hidden, F, 1)]
 
 
 def _normal(g, shape, sigma, mean=0.0):
@@ -82,8 +91,11 @@ def run_layer(T, hidden, heads, kv, d, F, ctx, window=0, seed=0):
     return run_chunks([T], hidden, heads, kv, d, F, ctx, window, seed)[0]
 
 
-def run_chunks(chunks, hidden, heads, kv, d, F, ctx, window=0, seed=0, scale=1.0):
-    """Runs the chunks one after the other; returns the outputs and the float64 layer's."""
+def run_chunks(chunks, hidden, heads, kv, d, F, ctx, window=0, seed=0, scale=1.0, phases=(BOTH,), peers=True, y=True,
+               pad=0, replays=0):
+    """Runs the chunks one after the other, the phases of each in turn; returns the outputs
+    and the float64 layer's. pad: elements of NaN after every matrix row. replays: the same calls
+    as a graph, replayed between eager runs, each with the eager run's bits."""
     T = sum(chunks)
     g = torch.Generator(device="cuda").manual_seed(100 + seed)
     dims = vt.vt_layer_dims(hidden=hidden, n_heads=heads, n_kv_heads=kv, head_dim=d, ffn=F, rms_eps=EPS,
@@ -91,13 +103,15 @@ def run_chunks(chunks, hidden, heads, kv, d, F, ctx, window=0, seed=0, scale=1.0
     spec = vt.vt_shard_spec_create(dims, [1.0], [1.0], 0)
     dims, info = vt.vt_shard_spec_query(spec)
     s = scale / math.sqrt(hidden)
-    ld = pack.round_up(F, 8)
-    w = {"g_attn": _normal(g, (hidden,), 0.1, 1.0), "g_ffn": _normal(g, (hidden,), 0.1, 1.0),
-         "wq": _normal(g, (heads * d, hidden), s), "wk": _normal(g, (kv * d, hidden), s),
-         "wv": _normal(g, (kv * d, hidden), s), "wo": _normal(g, (hidden, heads * d), s),
-         "wg": _normal(g, (F, hidden), s), "wu": _normal(g, (F, hidden), s)}
-    w["wd"] = torch.full((hidden, ld), math.nan, dtype=torch.float16, device="cuda")  # row padding: never read
-    w["wd"][:, :F] = _normal(g, (hidden, F), s)
+    w, full = {"g_attn": _normal(g, (hidden,), 0.1, 1.0), "g_ffn": _normal(g, (hidden,), 0.1, 1.0)}, {}
+    for n, rows, cols in (("wq", heads * d, hidden), ("wk", kv * d, hidden), ("wv", kv * d, hidden),
+                          ("wo", hidden, heads * d), ("wg", F, hidden), ("wu", F, hidden), ("wd", hidden, F)):
+        full[n] = torch.full((rows, pack.round_up(cols, 8) + pad), math.nan, dtype=torch.float16, device="cuda")
+        w[n] = full[n][:, :cols]  # row padding: never read
+        w[n].copy_(_normal(g, (rows, cols), s))
+    weights = pack.struct_of({**w, **full}, dims, info, full["wd"].shape[1])
+    for n in "qkvogud":
+        setattr(weights, "ld_" + n, full["w" + n].shape[1])
     cap = ctx + T + 2
     kc, vc = _normal(g, (kv, cap, d), 1.0), _normal(g, (kv, cap, d), 1.0)
     k0, v0 = kc.clone(), vc.clone()
@@ -106,19 +120,45 @@ def run_chunks(chunks, hidden, heads, kv, d, F, ctx, window=0, seed=0, scale=1.0
            for n in ("p_attn", "h", "p_ffn", "y")}
     ws = torch.zeros(vt.vt_workspace_size(spec, T, cap), dtype=torch.uint8, device="cuda")
     view = vt.vt_kv_view(k=kc.data_ptr(), v=vc.data_ptr(), capacity=cap, n_kv_heads=kv, head_dim=d, len=ctx)
-    t0 = 0
-    for n in chunks:
-        io = vt.vt_layer_io(x=x[t0:].data_ptr(), peer_attn=pa[t0:].data_ptr(), peer_ffn=pf[t0:].data_ptr(),
-                            attn_partial=out["p_attn"][t0:].data_ptr(), h=out["h"][t0:].data_ptr(),
-                            ffn_partial=out["p_ffn"][t0:].data_ptr(), y=out["y"][t0:].data_ptr())
-        vt.vt_layer_prefill_chunk(spec, pack.struct_of(w, dims, info, ld), view, io, n, ctx + t0, BOTH, ws.data_ptr(),
-                                  ws.numel(), torch.cuda.current_stream().cuda_stream)
-        t0 += n
+
+    def launch():
+        t0, view.len = 0, ctx
+        for n in chunks:
+            io = vt.vt_layer_io(x=x[t0:].data_ptr(), peer_attn=pa[t0:].data_ptr() if peers else None,
+                                peer_ffn=pf[t0:].data_ptr() if peers else None,
+                                attn_partial=out["p_attn"][t0:].data_ptr(), h=out["h"][t0:].data_ptr(),
+                                ffn_partial=out["p_ffn"][t0:].data_ptr(), y=out["y"][t0:].data_ptr() if y else None)
+            for phase in phases:
+                vt.vt_layer_prefill_chunk(spec, weights, view, io, n, ctx + t0, phase, ws.data_ptr(), ws.numel(),
+                                          torch.cuda.current_stream().cuda_stream)
+            t0 += n
+
+    launch()
+    if replays:
+        torch.cuda.synchronize()
+        eager = {n: t.clone() for n, t in out.items()}
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            launch()
+        for _ in range(replays):
+            for t in out.values():
+                t.fill_(7.0)
+            graph.replay()
+            torch.cuda.synchronize()
+            assert all(torch.equal(out[n], t) for n, t in eager.items())
+            launch()
+            torch.cuda.synchronize()
+            assert all(torch.equal(out[n], t) for n, t in eager.items())
+    if not peers:
+        pa, pf = pa * 0, pf * 0
     torch.cuda.synchronize()
     assert int(ws[vt.VT_WS_ERROR_WORD:vt.VT_WS_ERROR_WORD + 4].view(torch.int32)) == 0
     ref = _layer(w, k0, v0, x, pa, pf, heads, kv, d, F, ctx, window, out["h"][:T])
     for n in ("p_attn", "h", "p_ffn", "y"):
         assert (out[n][T] == 7.0).all(), n  # nothing past the chunk's rows
+        if n == "y" and not y:
+            assert (out[n] == 7.0).all()
+            continue
         _close(out[n][:T], ref[n], n)
     _close(kc[:, ctx:ctx + T], ref["k"], "keys")
     _close(vc[:, ctx:ctx + T], ref["v"], "values")
@@ -127,26 +167,63 @@ def run_chunks(chunks, hidden, heads, kv, d, F, ctx, window=0, seed=0, scale=1.0
     return out, ref
 
 
-# tokens, hidden, heads, KV heads, head_dim, FFN columns, context
+# tokens, hidden, heads, KV heads, head_dim, FFN columns, context; the tile edge and slices
+# of each GEMM: every epilogue of the 256 tile whole and in each number of slices
 GEMM_EDGES = [
-    (2305, 4104, 24, 24, 64, 4099, 5),     # QKV, gate/up, down unsplit; K ends 8 and 3 into a k-tile
-    (777, 8192, 24, 3, 128, 10609, 130),   # gate/up and down in 2 slices, the second with the partial k-tile
-    (4090, 4096, 16, 16, 128, 1031, 0),    # O unsplit
-    (900, 8192, 64, 8, 128, 520, 33),      # O in 2 slices
+    # QKV, O, down unsplit; K ends 8 and 3 into a k-tile
+    ((2305, 4104, 24, 24, 64, 4099, 5), [(256, 1), (256, 1), (128, 1), (256, 1)]),
+    # gate/up and down in 2 slices, the second with the partial k-tile
+    ((777, 8192, 24, 3, 128, 10609, 130), [(128, 2), (128, 1), (256, 2), (256, 2)]),
+    ((4090, 4096, 16, 16, 128, 1031, 0), [(256, 1), (256, 1), (256, 1), (128, 1)]),
+    ((900, 8192, 64, 8, 128, 520, 33), [(256, 3), (256, 2), (128, 3), (128, 1)]),
+    ((1290, 3080, 64, 8, 128, 520, 2), [(256, 1), (256, 3), (128, 2), (128, 1)]),
+    ((777, 3080, 64, 8, 128, 520, 0), [(256, 1), (256, 4), (128, 4), (128, 1)]),
+    # QKV in 2 slices, the second with a k-tile of 8
+    ((900, 5128, 32, 32, 64, 520, 70), [(256, 2), (128, 2), (128, 3), (128, 1)]),
+    ((900, 8192, 8, 8, 128, 520, 1), [(256, 4), (128, 1), (128, 3), (128, 1)]),
+    # one row of token tiles, its second half of 12 tokens
+    ((140, 8192, 8, 1, 128, 17003, 9), [(128, 4), (128, 2), (256, 3), (128, 4)]),
+    ((385, 8192, 8, 1, 128, 2700, 0), [(128, 4), (128, 1), (256, 4), (128, 1)]),
+    ((1290, 3080, 8, 1, 128, 5504, 3), [(128, 2), (128, 1), (128, 1), (256, 3)]),
+    # down in 4 slices, the last with a k-tile of 7
+    ((777, 3080, 8, 1, 128, 9351, 3), [(128, 3), (128, 1), (128, 1), (256, 4)]),
 ]
 
 
-@pytest.mark.parametrize("shape", GEMM_EDGES, ids=[f"T{s[0]}-H{s[1]}-F{s[5]}" for s in GEMM_EDGES])
-def test_gemm_tile_edges(shape):
+@pytest.mark.parametrize("shape,plan", GEMM_EDGES, ids=[f"T{s[0]}-H{s[1]}-F{s[5]}" for s, _ in GEMM_EDGES])
+def test_gemm_tile_edges(shape, plan):
+    assert gemm_plan(*shape[:6]) == plan
     run_layer(*shape)
+
+
+@pytest.mark.parametrize("shape,plan", [GEMM_EDGES[i] for i in (0, 1, 2)], ids=["down", "gate-up-split", "O"])
+def test_gemm_tile_phases_apart(shape, plan):
+    """The phases as calls of their own (no gain and no sums of squares between them), no
+    peers, no y, and rows of every matrix with padding."""
+    assert gemm_plan(*shape[:6]) == plan
+    run_chunks([shape[0]], *shape[1:], seed=3, phases=(vt.VT_ATTN, vt.VT_FFN), peers=False, y=False, pad=24)
+
+
+@pytest.mark.parametrize("i", [2, 11])
+def test_gemm_tiles_repeat_is_bitwise(i):
+    a, b = run_layer(*GEMM_EDGES[i][0]), run_layer(*GEMM_EDGES[i][0])
+    for n in a:
+        assert torch.equal(a[n], b[n]), n
 
 
 def test_gemm_split_repeat_is_bitwise():
     """The slices' sums are added in slice order, whichever arrives last."""
-    a = run_layer(*GEMM_EDGES[1])
-    b = run_layer(*GEMM_EDGES[1])
+    a = run_layer(*GEMM_EDGES[1][0])
+    b = run_layer(*GEMM_EDGES[1][0])
     for n in a:
         assert torch.equal(a[n], b[n]), n
+
+
+def test_gemm_tile_graph_replays():
+    """Two chunks, split on the 256 tile and with the shared-block attention, as one graph."""
+    shape = (4104, 40, 8, 128, 6001)
+    assert [p[0] for p in gemm_plan(1290, *shape)] == [256, 256, 128, 256] and shared_blocks(1290, 40, 128, 50)
+    run_chunks([1290, 900], *shape, 50, seed=4, replays=3)
 
 
 # attention with 128 queries per workgroup: enough heads and tokens for it, the
