@@ -6,15 +6,15 @@
 // ones. Pure data movement: every value is copied bit for bit.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "device.hpp"
 #include "internal.hpp"
 
 namespace vt {
 namespace rp {
 
-constexpr int CT = 256;
-constexpr int CU = 4;         // 16-byte chunks per thread, all loaded before the first is stored
-constexpr int CCH = CT * CU;  // chunks per workgroup
+constexpr int CT = 256;  // threads per workgroup, one 16-byte chunk each
 
 // The 16 bytes that start 2 * sh bytes into lo (sh in 0..7), continued by hi.
 __device__ __forceinline__ u32x4 shifted(u32x4 lo, u32x4 hi, int sh) {
@@ -34,58 +34,75 @@ __device__ __forceinline__ u32x4 shifted(u32x4 lo, u32x4 hi, int sh) {
 
 // dst[r][c] = src[r][c0 + c] for c < cols and 0 for cols <= c < dcols
 // (fp16, strides in elements; dst rows and dcols in whole 8-element chunks
-// of 16 bytes). A workgroup takes ``rpw`` whole rows of ``nch`` chunks, or CCH
-// chunks of one longer row (``segs`` workgroups per row). ALIGNED: c0 is a
-// multiple of 8 and a whole chunk is one 16-byte load; else a chunk comes from
-// the two aligned chunks it lies across, shifted together (5120 x 8294
-// of a Wd: 35 us, 4.8 TB/s; 47 us with eight 2-byte loads per chunk). Chunks at the end of the
-// row's cols, past which nothing is read, go element by element.
-template <bool ALIGNED>
+// of 16 bytes). A workgroup takes ``rpw`` whole rows of ``nch`` chunks (x counts
+// such groups), or CT chunks of every gridDim.y-th longer row (x counts a row's
+// segments). ALIGNED: c0 is a multiple of 8 and a whole chunk is one 16-byte
+// load; else a chunk comes from the two aligned chunks it lies across, shifted
+// together (5120 x 8294 of a Wd: 35 us; 47 us with eight 2-byte loads per
+// chunk). Chunks at the end of the row's cols, past which nothing is read, go
+// element by element.
+// One chunk per thread: with four, a small copy had too few waves to hide its one
+// round trip (KV heads of 3 x 2048 x 128: 5.2 us against 4.2 for one, 8 x 16 x 128: 4.7
+// against 3.8).
+// STREAM: 1 stores past the caches, 2 loads past them as well.
+template <bool ALIGNED, int STREAM>
 __global__ void __launch_bounds__(CT) copy2d_kernel(const uint16_t* __restrict__ src, int64_t lds, int64_t c0,
                                                     uint16_t* __restrict__ dst, int64_t ldd, int rows, int cols,
-                                                    int nch, int rpw, int segs, uint32_t magic) {
-  const int64_t r0 = segs > 1 ? blockIdx.x / segs : static_cast<int64_t>(blockIdx.x) * rpw;
-  const int ch0 = segs > 1 ? static_cast<int>(blockIdx.x % segs) * CCH : 0;
-  const int nrow = static_cast<int>(min(static_cast<int64_t>(rpw), rows - r0));
+                                                    int nch, int rpw, uint32_t magic) {
   const int sh = ALIGNED ? 0 : static_cast<int>(c0 % 8);
-  u32x4 v[CU];
-  int64_t out[CU];
-#pragma unroll
-  for (int u = 0; u < CU; ++u) {
-    const int n = u * CT + static_cast<int>(threadIdx.x);
-    // n / nch for n < 1024 (magic = ceil(2^20 / nch), exact as n nch < 2^20)
-    const int dr = segs > 1 ? 0 : static_cast<int>((static_cast<uint32_t>(n) * magic) >> 20);
-    const int ch = segs > 1 ? ch0 + n : n - dr * nch;
-    out[u] = -1;
-    if (dr >= nrow || ch >= nch) continue;
-    const int c = ch * 8;
-    out[u] = (r0 + dr) * ldd + c;
-    const uint16_t* s = src + (r0 + dr) * lds + c0 + c;
+  const int n = static_cast<int>(threadIdx.x);
+  int64_t r = blockIdx.y;
+  int ch = static_cast<int>(blockIdx.x) * CT + n;
+  if (rpw > 0) {
+    // n / nch for n < 256 (magic = ceil(2^16 / nch), exact as n nch < 2^16)
+    const int dr = static_cast<int>((static_cast<uint32_t>(n) * magic) >> 16);
+    r = static_cast<int64_t>(blockIdx.x) * rpw + dr;
+    ch = n - dr * nch;
+    if (dr >= rpw) return;
+  }
+  if (ch >= nch) return;
+  const int c = ch * 8;
+  for (; r < rows; r += gridDim.y) {
+    const uint16_t* s = src + r * lds + c0 + c;
+    u32x4 v;
     if (c + (ALIGNED ? 8 : 16 - sh) <= cols) {
-      if (ALIGNED) v[u] = load_stream(s);
-      else v[u] = shifted(load16(s - sh), load16(s - sh + 8), sh);
+      if (ALIGNED) v = STREAM == 2 ? load_stream(s) : load16(s);
+      else v = shifted(load16(s - sh), load16(s - sh + 8), sh);
     } else {
       uint16_t h[8];
 #pragma unroll
       for (int e = 0; e < 8; ++e) h[e] = c + e < cols ? s[e] : 0;
-      v[u] = pack8(h);
+      v = pack8(h);
     }
+    u32x4* d = reinterpret_cast<u32x4*>(dst + r * ldd + c);
+    if (STREAM) __builtin_nontemporal_store(v, d);
+    else *d = v;
+    if (rpw > 0) return;
   }
-#pragma unroll
-  for (int u = 0; u < CU; ++u)
-    if (out[u] >= 0) __builtin_nontemporal_store(v[u], reinterpret_cast<u32x4*>(dst + out[u]));
 }
+
+// Bytes from which a copy stores past the caches, and loads past them as well. What is
+// copied is not read again soon, but a small copy's target stays in the last-level
+// cache and is cheaper to write there. Layer shards packed over four rotated
+// sets of buffers, plain / stores / both: matrices of 1-6 MB (hidden 1032) 19.1 / 20.8
+// / 20.8 us; 9 MB 35.3 / 27.4 / 29.4; KV heads of 67 MB 49.2 / 47.6 / 46.0 (one set: 41.8 / 41.6
+// / 44.6); 57 MB 105.9 / 98.0 / 95.7; 290 MB 296.8 / 274.5 / 267.0.
+constexpr int64_t kStoreStream = int64_t(4) << 20, kLoadStream = int64_t(72) << 20;
 
 static vt_status copy2d(const uint16_t* src, int64_t lds, int64_t c0, uint16_t* dst, int64_t ldd, int rows, int cols,
                         int dcols, hipStream_t s) {
   if (rows <= 0 || dcols <= 0) return VT_OK;
-  const int nch = dcols / 8;
-  const int segs = (nch + CCH - 1) / CCH, rpw = segs > 1 ? 1 : CCH / nch;
-  const int64_t grid = segs > 1 ? static_cast<int64_t>(rows) * segs : (static_cast<int64_t>(rows) + rpw - 1) / rpw;
-  const uint32_t magic = ((1u << 20) + nch - 1) / nch;
-  auto* kernel = c0 % 8 == 0 ? copy2d_kernel<true> : copy2d_kernel<false>;
-  hipLaunchKernelGGL(kernel, dim3(static_cast<uint32_t>(grid)), dim3(CT), 0, s, src, lds, c0, dst, ldd, rows, cols, nch,
-                     rpw, segs, magic);
+  const int nch = dcols / 8, rpw = nch > CT ? 0 : CT / nch;
+  const dim3 grid(static_cast<uint32_t>(rpw > 0 ? (static_cast<int64_t>(rows) + rpw - 1) / rpw : (nch + CT - 1) / CT),
+                  rpw > 0 ? 1 : std::min(rows, 65535));
+  const uint32_t magic = ((1u << 16) + nch - 1) / nch;
+  const int64_t bytes = static_cast<int64_t>(rows) * dcols * 2;
+  auto pick = [&](auto* plain, auto* store, auto* both) {
+    return bytes >= kLoadStream ? both : (bytes >= kStoreStream ? store : plain);
+  };
+  auto* kernel = c0 % 8 == 0 ? pick(copy2d_kernel<true, 0>, copy2d_kernel<true, 1>, copy2d_kernel<true, 2>)
+                             : pick(copy2d_kernel<false, 0>, copy2d_kernel<false, 1>, copy2d_kernel<false, 1>);
+  hipLaunchKernelGGL(kernel, grid, dim3(CT), 0, s, src, lds, c0, dst, ldd, rows, cols, nch, rpw, magic);
   hipError_t e = hipGetLastError();
   return e == hipSuccess ? VT_OK : fail(VT_ERR_HIP, "copy launch: %s", hipGetErrorString(e));
 }

@@ -209,3 +209,31 @@ def test_shard_pack_column_offsets(F, c0):
     assert torch.equal(new.tensors["wd"][:, :n], full["wd"][:, c0:F])
     assert not new.tensors["wd"][:, n:pack.round_up(n, 8)].any()
     assert torch.equal(new.tensors["wg"][:n], full["wg"][c0:]) and torch.equal(new.tensors["wo"], full["wo"][:, 64:])
+
+
+def test_shard_pack_many_long_rows():
+    """More rows than a grid's second dimension, each of several workgroups, aligned and
+    not, of a size that goes past the caches."""
+    H, F, c0 = 2056, 70011, 3
+    dims = vt.vt_layer_dims(hidden=H, n_heads=2, n_kv_heads=2, head_dim=64, ffn=F, rms_eps=1e-5, rope_base=1e4,
+                            window=0)
+    spec = vt.vt_shard_spec_create(dims, [0.5, 0.5], [c0 / F, 1.0 - c0 / F], 1)
+    dims, info = vt.vt_shard_spec_query(spec)
+    assert info.col_begin == c0 and info.n_cols == F - c0
+    g = torch.Generator(device="cuda").manual_seed(6)
+    normal = lambda *shape: torch.empty(shape, dtype=torch.float16, device="cuda").normal_(generator=g)
+    ld = pack.round_up(F, 8)
+    full = {"g_attn": normal(H), "g_ffn": normal(H), "wq": normal(128, H), "wk": normal(128, H),
+            "wv": normal(128, H), "wo": normal(H, 128), "wg": normal(F, H), "wu": normal(F, H), "wd": normal(H, ld)}
+    new = pack.alloc_shard(dims, info)
+    for t in new.tensors.values():
+        t.fill_(7.0)
+    vt.vt_shard_pack(spec, pack.struct_of(full, dims, vt.vt_shard_info(0, 2, 0, 2, 0, F), ld), new.struct,
+                     torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    n = F - c0
+    assert torch.equal(new.tensors["wg"], full["wg"][c0:]) and torch.equal(new.tensors["wu"], full["wu"][c0:])
+    assert torch.equal(new.tensors["wd"][:, :n], full["wd"][:, c0:F])
+    assert not new.tensors["wd"][:, n:].any()
+    for name in ("g_attn", "g_ffn"):
+        assert torch.equal(new.tensors[name], full[name])
