@@ -1758,7 +1758,7 @@ Split small_split(int M, int N, int K) {
 
 // Which tile: the 128 one as split above or the 256 one with its best slice
 // count, by the modelled times of both (microseconds). Fitted to the traced
-// times of both kernels in 1-4 slices on 114 drawn and named layers (hidden 512 to
+// times of both kernels in 1-4 slices on 194 drawn and named layers (hidden 512 to
 // 8192, 131 to 4096 tokens; median error 4%, nine in ten within 12%).
 // * A row of B whose length is no multiple of 64 bytes (K is no multiple of 32 after
 //   rounding up to 8) straddles the memory's lines: more per k-tile for both, a
@@ -1772,7 +1772,7 @@ Split small_split(int M, int N, int K) {
 // * A modelled small-tile time below kSmallEnough is taken without a look at the other: no
 //   shape measured below it was faster on the large tile, whose first loads and
 //   epilogue take 20-35 us.
-// Over the shapes measured (one time per GEMM): 63.6 ms with this rule, 63.9 with
+// Over the products measured (one time each): 63.6 ms with this rule, 63.9 with
 // whole rounds of 256 workgroups as the large tile's only cost, 70.3 on the small
 // tile alone, 63.3 with the better of both each time.
 constexpr double kSmallEnough = 60.0;
@@ -1944,10 +1944,10 @@ vt_status launch_gemm(pf::GemmArgs a, float* P, unsigned* cnt, unsigned* err, hi
 // is longer than its last), or, from 257 workgroups on, one of the first round and
 // the one that follows it, or the average. attn_prefill_kernel's workgroups of
 // 32 queries are many and short: the average. Fitted to both kernels' times on 159
-// chunks (1 to 128 heads, contexts of 0 to 8140, windows of 128 and 1024, 128
-// to 4096 tokens; median error 5%). A count of workgroups alone (224) took the shared blocks
+// chunks of 100 workgroups and more (4 to 128 heads, contexts of 0 to 8140, windows of
+// 128 and 1024, 130 to 4096 tokens; median error 5%). A count of workgroups alone (224) took the shared blocks
 // at head size 64, 8 heads and 3585 tokens from position 0, whose last query
-// block walks 113 key blocks by itself: 73 us against 53. All chunks measured:
+// block walks 113 key blocks by itself: 73 us against 53. All 200 chunks measured:
 // 12.7 ms with this rule, 12.8 with the count, 14.9 without the shared blocks.
 bool long_attention(int T, int nq, int d, int pos0, int window) {
   struct Fit {
