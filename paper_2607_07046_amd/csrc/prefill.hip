@@ -1758,47 +1758,47 @@ Split small_split(int M, int N, int K) {
 
 // Which tile: the 128 one as split above or the 256 one with its best slice
 // count, by the modelled times of both (microseconds). Fitted to the traced
-// times of both kernels in 1-4 slices on 194 drawn and named layers (hidden 512 to
-// 8192, 131 to 4096 tokens; median error 4%, nine in ten within 12%).
+// times of both kernels in 1-4 slices on the GEMMs of 494 drawn and named layers (hidden
+// 512 to 8192, 128 to 4096 tokens; median error 4%, nine in ten within 10%).
+// * Workgroups go to the XCDs in turn by units of 8 (the walk above): rounds are those of
+//   the fullest XCD, 64 workgroups on its 32 compute units, or 32 of the large tile.
+//   7 x 33 large tiles are two rounds (5 x 7 on one XCD): 208 us against 176 for the
+//   small tile.
 // * A row of B whose length is no multiple of 64 bytes (K is no multiple of 32 after
-//   rounding up to 8) straddles the memory's lines: more per k-tile for both, a
-//   fifth more for the large tile (hidden 6000, 2035 tokens, gate/up: 353 us against
-//   290 for the small tile).
-// * The large tile runs one workgroup per compute unit and an XCD's share in its
-//   own 32: a round begins when the fullest XCD has more. 7 x 33 tiles are two
-//   rounds (5 x 7 on one XCD): 208 us against 176 for the small tile.
-// * Both read B once (per byte), and O and down move 10 bytes per output in
-//   the epilogue, of which the large tile hides less.
+//   rounding up to 8) straddles the memory's lines: a tenth more per k-tile for the small
+//   tile, a fifth more for the large one (hidden 6000, 2035 tokens, gate/up in one slice: 353
+//   us against 290 for the small tile).
+// * B is read once (per byte), and O and down move 10 bytes per output in the
+//   epilogue, of which the large tile hides less.
 // * A modelled small-tile time below kSmallEnough is taken without a look at the other: no
-//   shape measured below it was faster on the large tile, whose first loads and
+//   product measured below 60 us was faster on the large tile, whose first loads and
 //   epilogue take 20-35 us.
-// Over the products measured (one time each): 63.6 ms with this rule, 63.9 with
-// whole rounds of 256 workgroups as the large tile's only cost, 70.3 on the small
-// tile alone, 63.3 with the better of both each time.
-constexpr double kSmallEnough = 60.0;
+// All products measured (one time each): 110.0 ms with this rule, 124.6 on the small
+// tile alone, 109.7 with the better of both each time; the worst miss is 14% of one
+// product (gate/up of 1749 tokens at hidden 5864: 330 us against 289).
+constexpr double kSmallEnough = 55.0;
 
 double misaligned(int K) { return (K + 7) / 8 * 8 % 32 != 0 ? 1.0 : 0.0; }
 // Outputs and weights in millions; rows rounded up, so that the choice depends on M only
 // through its number of 128-row tiles.
 double outputs(int M, int N) { return (M + pf::GBM - 1) / pf::GBM * static_cast<double>(pf::GBM) * N * 1e-6; }
 double weights(int N, int K) { return static_cast<double>(N) * K * 1e-6; }
+int64_t fullest_xcd(const Split& c) { return (c.n_tiles * c.splits + 7) / 8 * static_cast<int64_t>(c.m_tiles); }
 
 double small_us(const Split& c, int M, int N, int K, bool residual) {
-  const double two = 1.18 + 0.14 * misaligned(K), one = 0.60 + 0.07 * misaligned(K);
-  const int64_t tiles = std::max(1, c.m_tiles * c.n_tiles), groups = tiles * c.splits, half = pf::GEMM_SLOTS / 2;
-  const int64_t rest = groups % pf::GEMM_SLOTS;
-  double t = static_cast<double>(groups / pf::GEMM_SLOTS) * c.kps * two + 16.0;
-  if (rest > half) t += c.kps * (one + (two - one) * static_cast<double>(rest - half) / half);
+  const double two = 1.153 + 0.111 * misaligned(K), one = 0.629 + 0.055 * misaligned(K);
+  const int64_t rounds = fullest_xcd(c) / 64, rest = fullest_xcd(c) % 64;
+  double t = static_cast<double>(rounds) * c.kps * two + 10.7;
+  if (rest > 32) t += c.kps * (one + (two - one) * static_cast<double>(rest - 32) / 32);
   else if (rest > 0) t += c.kps * one;
-  return t + 0.016 * static_cast<double>(c.splits - 1) * static_cast<double>(tiles) +
-         (residual ? 1.0 * outputs(M, N) : 0.0) + 0.031 * weights(N, K);
+  return t + 0.0208 * (c.splits - 1) * c.m_tiles * c.n_tiles + (residual ? 1.39 * outputs(M, N) : 0.0) +
+         0.068 * weights(N, K);
 }
 
 double big_us(const Split& c, int M, int N, int K, bool residual) {
-  const int xcd = (c.n_tiles * c.splits + 7) / 8 * c.m_tiles;  // workgroups of the fullest XCD
-  double t = static_cast<double>((xcd + 31) / 32) * (c.kps * (1.27 + 0.27 * misaligned(K)) + 3.0) +
-             (residual ? 3.1 : 1.6) * outputs(M, N) + 0.16 * weights(N, K);
-  if (c.splits > 1) t += 15.7 + 0.079 * (c.splits - 1) * c.m_tiles * c.n_tiles;
+  double t = static_cast<double>((fullest_xcd(c) + 31) / 32) * (c.kps * (1.286 + 0.258 * misaligned(K)) + 2.77) +
+             (residual ? 2.90 : 1.41) * outputs(M, N) + 0.153 * weights(N, K);
+  if (c.splits > 1) t += 15.4 + 0.0821 * (c.splits - 1) * c.m_tiles * c.n_tiles;
   return t;
 }
 

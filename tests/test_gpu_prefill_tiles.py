@@ -179,14 +179,14 @@ GEMM_EDGES = [
     ((1290, 3080, 64, 8, 128, 520, 2), [(256, 1), (256, 3), (128, 2), (128, 1)]),
     ((777, 3080, 64, 8, 128, 520, 0), [(256, 1), (256, 4), (128, 4), (128, 1)]),
     # QKV in 2 slices, the second with a k-tile of 8
-    ((900, 5128, 32, 32, 64, 520, 70), [(256, 2), (128, 2), (128, 3), (128, 1)]),
+    ((579, 5128, 26, 26, 128, 520, 70), [(256, 2), (128, 2), (128, 4), (128, 1)]),
     ((900, 8192, 8, 8, 128, 520, 1), [(256, 4), (128, 1), (128, 3), (128, 1)]),
     # one row of token tiles, its second half of 12 tokens
     ((140, 8192, 8, 1, 128, 17003, 9), [(128, 4), (128, 2), (256, 3), (128, 4)]),
     ((385, 8192, 8, 1, 128, 2700, 0), [(128, 4), (128, 1), (256, 4), (128, 1)]),
     ((1290, 3080, 8, 1, 128, 5504, 3), [(128, 2), (128, 1), (128, 1), (256, 3)]),
     # down in 4 slices, the last with a k-tile of 7
-    ((777, 3080, 8, 1, 128, 9351, 3), [(128, 3), (128, 1), (128, 1), (256, 4)]),
+    ((579, 3080, 8, 1, 128, 9351, 3), [(128, 4), (128, 2), (256, 1), (256, 4)]),
 ]
 
 
